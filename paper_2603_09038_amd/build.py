@@ -26,7 +26,7 @@ def _units():
     units = []
     for p in range(1, 9):
         units.append(("k_apply.hip", f"k_apply_p{p}.o", [f"-DHEXPA_APPLY_P={p}"]))
-    for src in ("k_setup.hip", "k_diag.hip", "k_vec.hip", "k_debug.hip", "k_nn.hip", "noalloc.hip", "k_mixed.hip"):
+    for src in ("k_setup.hip", "k_diag.hip", "k_vec.hip", "k_debug.hip", "k_nn.hip", "k_nn_train.hip", "noalloc.hip", "k_mixed.hip"):
         units.append((src, src.replace(".hip", ".o"), []))
     for src in ("api.cpp", "tables.cpp", "learned.cpp", "mixed.cpp"):
         units.append((src, src.replace(".cpp", ".o"), ["-x", "hip"]))

@@ -15,31 +15,35 @@ constexpr int kNetParams = kNetW1 + kNetCh + kNetW2 + kNetCh + kNetW3 + 1;
 constexpr int kNetOffW1 = 0, kNetOffB1 = kNetW1, kNetOffW2 = kNetOffB1 + kNetCh, kNetOffB2 = kNetOffW2 + kNetW2,
               kNetOffW3 = kNetOffB2 + kNetCh, kNetOffB3 = kNetOffW3 + kNetW3;
 
+// floats of the packed FP32 weights (the five lane-ordered tables of k_nn_train.hip)
+constexpr int kNetPack32 = 64 * (3 * 27 * 4 + 9 * 2 + 9);
+
+// Tile edge n = p + 1 in {3, 4, 5}.  The FP32 pass works on nn_tiles(nelem) tiles: every
+// element's tile for +r and for -r, in groups of sixteen (eight elements), the last group
+// filled up with zero tiles; layouts in k_nn_train.hip.
+int64_t nn_tiles(int64_t nelem);
 // Floats of weight-gradient partial sums the backward pass needs.
 int64_t nn_partial_floats();
-
-// Tile edge n = p + 1 in {3, 4, 5}.  Activations [e][c][n^3].
-// wt: kNetW1 + kNetW2 + kNetW3 floats of transposed weights.
+// wt: kNetPack32 floats, which receive the packed weights (the backward pass reads them).
 hipError_t nn_forward(int n, int64_t nelem, const float *params, float *wt, const float *x0, float *a1, float *a2,
                       float *out, hipStream_t s);
-// grads += dL/dparams given gout = dL/dout; ga1, ga2 are [e][16][n^3] work arrays,
-// wt holds kNetW2 floats, partial nn_partial_floats().
-hipError_t nn_backward(int n, int64_t nelem, const float *params, const float *x0, const float *a1, const float *a2,
-                       const float *gout, float *ga2, float *ga1, float *grads, float *wt, float *partial,
-                       hipStream_t s);
+// grads += dL/dparams given gout = dL/dout; ga1, ga2 are work arrays of an activation's size,
+// partial nn_partial_floats(); wt as nn_forward of the same parameters left it.
+hipError_t nn_backward(int n, int64_t nelem, const float *wt, const float *x0, const float *a1, const float *a2,
+                       const float *gout, float *ga2, float *ga1, float *grads, float *partial, hipStream_t s);
 // Inference in one kernel with FP16 MFMA (FP32 accumulation): z += W G^T (s_e NN(...)).
 // wpack: nn_pack16_bytes() of device scratch for the lane-ordered FP16 weights.
 int64_t nn_pack16_bytes();
 hipError_t nn_infer16(int n, int64_t nelem, const float *params, void *wpack, const double *r, const int32_t *emap,
                       const float *logk, const double *inv_mult, double scale, double *z, hipStream_t s);
-// x0 tiles [2 nelem][2][n^3]: tile e = [G_e r / s_e, logk_e], tile nelem + e = [-G_e r / s_e,
-// logk_e]; s_e = RMS of G_e r (1 where it vanishes).
+// x0 tiles: channel 0 = +-G_e r / s_e, channel 1 = logk_e; s_e = RMS of G_e r (1 where it
+// vanishes).
 hipError_t nn_input(int n, int64_t nelem, const double *r, const int32_t *emap, const float *logk, float *x0,
                     float *s, hipStream_t st);
-// z[g] += scale s_e (out_e - out_{nelem+e}) / 2 inv_mult[g] over all element nodes (the odd part).
+// z[g] += scale s_e (out(+r)_e - out(-r)_e) / 2 inv_mult[g] over all element nodes (the odd part).
 hipError_t nn_output(int n, int64_t nelem, const float *out, const float *s, const int32_t *emap,
                      const double *inv_mult, double scale, double *z, hipStream_t st);
-// gout_e = s_e inv_mult[g] gz[g] / 2, gout_{nelem+e} = -gout_e (adjoint of nn_output).
+// gout(+r)_e = s_e inv_mult[g] gz[g] / 2, gout(-r)_e its negative (adjoint of nn_output).
 hipError_t nn_output_grad(int n, int64_t nelem, const double *gz, const float *s, const int32_t *emap,
                           const double *inv_mult, float *gout, hipStream_t st);
 // inv_mult[g] = 1 / (number of elements holding g).

@@ -1,13 +1,9 @@
-// Kernels of the learned preconditioner: the per-element 3-layer convolutional network
-// on the (p+1)^3 nodal tile (3x3x3 cross-correlation, zero padding 1, bias, ReLU between
-// layers), its backward pass and Adam, the tile gather/normalisation and the averaged
-// scatter of the element outputs, and the p=1 coarse level of the two-level preconditioner.
-//
-// Activations are stored [element][channel][point], point = i + N j + N^2 k (the
+// Kernels of the learned preconditioner: the FP16 inference of its per-element 3-layer
+// convolutional network on the (p+1)^3 nodal tile (3x3x3 cross-correlation, zero padding 1,
+// bias, ReLU between layers; the FP32 forward and backward are in k_nn_train.hip), Adam, and
+// the p=1 coarse level of the two-level preconditioner.  Tile points are i + N j + N^2 k (the
 // operator's local node order); weights are [c_out][c_in][tap], tap = tx + 3 ty + 9 tz
-// reading the neighbour (i + tx - 1, j + ty - 1, k + tz - 1).  Work tiles sit in LDS with
-// a guard band on both sides so every shifted read is in bounds; reads that fall outside
-// the element are multiplied by 0 (zero padding).
+// reading the neighbour (i + tx - 1, j + ty - 1, k + tz - 1).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -20,245 +16,6 @@ namespace hexpa {
 namespace {
 
 inline unsigned nblk(int64_t n) { return (unsigned)((n + 255) / 256); }
-
-template <int N>
-struct Tile {
-    static constexpr int P = N * N * N;
-    static constexpr int GUARD = 1 + N + N * N;  // largest |offset| of a 3x3x3 neighbour
-    // elements per workgroup and workgroup size (a multiple of the wave size)
-    static constexpr int EPB = N == 3 ? 4 : (N == 4 ? 4 : 2);
-    static constexpr int THREADS = ((EPB * P + 63) / 64) * 64;
-    __host__ __device__ static constexpr int off(int tap)
-    {
-        return (tap % 3 - 1) + N * ((tap / 3) % 3 - 1) + N * N * (tap / 9 - 1);
-    }
-};
-
-// 0/1 factors of the 27 neighbours of point pt (1 inside the tile).
-template <int N>
-__device__ inline void tap_mask(int pt, float (&mk)[27])
-{
-    const int i = pt % N, j = (pt / N) % N, k = pt / (N * N);
-    const float mx[3] = {i > 0 ? 1.f : 0.f, 1.f, i < N - 1 ? 1.f : 0.f};
-    const float my[3] = {j > 0 ? 1.f : 0.f, 1.f, j < N - 1 ? 1.f : 0.f};
-    const float mz[3] = {k > 0 ? 1.f : 0.f, 1.f, k < N - 1 ? 1.f : 0.f};
-#pragma unroll
-    for (int t = 0; t < 27; ++t) mk[t] = mx[t % 3] * my[(t / 3) % 3] * mz[t / 9];
-}
-
-// out[e][o][pt] = bias[o] + sum_c sum_tap Wt[c][tap][o] in[e][c][pt + off(tap)]  (zero padded),
-// then ReLU (RELU) or a multiply by [a_mask > 0] (MASK, the backward of a ReLU).
-// Wt is the weight tensor already transposed to [c][tap][o]; bias may be null.
-template <int N, int CIN, int COUT, bool RELU, bool MASK>
-__global__ __launch_bounds__(Tile<N>::THREADS) void k_conv(int64_t nelem, const float *__restrict__ in,
-                                                           const float *__restrict__ Wt,
-                                                           const float *__restrict__ bias,
-                                                           const float *__restrict__ a_mask, float *__restrict__ out)
-{
-    using T = Tile<N>;
-    constexpr int NW = CIN * 27 * COUT, NX = T::EPB * CIN * T::P;
-    __shared__ float sw[NW];
-    __shared__ float sx[T::GUARD + NX + T::GUARD];
-    const int t = threadIdx.x;
-    const int64_t e0 = (int64_t)blockIdx.x * T::EPB;
-    const int64_t nin = std::min((int64_t)T::EPB, nelem - e0) * CIN * T::P;
-    for (int i = t; i < NW; i += T::THREADS) sw[i] = Wt[i];
-    for (int i = t; i < T::GUARD; i += T::THREADS) sx[i] = sx[T::GUARD + NX + i] = 0.f;
-    for (int i = t; i < NX; i += T::THREADS) sx[T::GUARD + i] = i < nin ? in[e0 * CIN * T::P + i] : 0.f;
-    __syncthreads();
-    const int el = t / T::P, pt = t % T::P;
-    if (el >= T::EPB || e0 + el >= nelem) return;
-    float mk[27];
-    tap_mask<N>(pt, mk);
-    float acc[COUT];
-#pragma unroll
-    for (int o = 0; o < COUT; ++o) acc[o] = bias ? bias[o] : 0.f;
-    const float *xs = sx + T::GUARD + el * CIN * T::P + pt;
-#pragma unroll 1
-    for (int c = 0; c < CIN; ++c) {
-        const float *xc = xs + c * T::P;
-        const float *wc = sw + c * 27 * COUT;
-#pragma unroll
-        for (int tap = 0; tap < 27; ++tap) {
-            const float v = xc[T::off(tap)] * mk[tap];
-#pragma unroll
-            for (int o = 0; o < COUT; ++o) acc[o] = fmaf(wc[tap * COUT + o], v, acc[o]);
-        }
-    }
-    const int64_t ob = (e0 + el) * COUT * T::P + pt;
-#pragma unroll
-    for (int o = 0; o < COUT; ++o) {
-        float v = acc[o];
-        if (RELU) v = fmaxf(v, 0.f);
-        if (MASK) v = a_mask[ob + o * T::P] > 0.f ? v : 0.f;
-        out[ob + o * T::P] = v;
-    }
-}
-
-// Wt[c][tap][o] = W[o][c][tap] (forward) or, for the input gradient, the flipped
-// adjoint Wt[o][tap][c] = W[o][c][26 - tap] read as a (COUT -> CIN) convolution.
-__global__ void k_transpose_w(const float *__restrict__ W, int cout, int cin, int adjoint, float *__restrict__ Wt)
-{
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= cout * cin * 27) return;
-    const int tap = i % 27, c = (i / 27) % cin, o = i / (27 * cin);
-    if (!adjoint) Wt[(c * 27 + tap) * cout + o] = W[i];
-    else Wt[(o * 27 + (26 - tap)) * cin + c] = W[i];
-}
-
-// Weight/bias gradient partial sums: dW[o][c][tap] = sum_e sum_pt dout[e][o][pt] in[e][c][pt + off(tap)],
-// db[o] = sum dout.  Thread = (c, group of OB outputs, slice of points); workgroup g
-// handles elements g, g + G, ...; row (g, slice) of `partial` receives the thread sums.
-template <int CIN, int COUT>
-struct WgradShape {
-    static constexpr int OB = COUT >= 4 ? 4 : 1;
-    static constexpr int NPAIR = CIN * (COUT / OB);
-    static constexpr int SL = 256 / NPAIR;
-    static constexpr int NT = COUT * CIN * 27 + COUT;
-    static_assert(COUT % OB == 0 && NPAIR <= 256 && 256 % NPAIR == 0, "thread layout");
-};
-constexpr int kWgradBlocks = 768;  // three workgroups per CU: the 16x16 layer's 162 registers allow three
-
-template <int N, int CIN, int COUT>
-__global__ __launch_bounds__(256) void k_conv_wgrad(int64_t nelem, const float *__restrict__ in,
-                                                    const float *__restrict__ dout, float *__restrict__ partial)
-{
-    using T = Tile<N>;
-    using S = WgradShape<CIN, COUT>;
-    constexpr int OB = S::OB, NX = CIN * T::P;
-    __shared__ float sx[T::GUARD + NX + T::GUARD];
-    __shared__ float sd[COUT * T::P];
-    const int t = threadIdx.x;
-    const int pair = t % S::NPAIR, sl = t / S::NPAIR;
-    const int c = pair % CIN, og = pair / CIN;
-    float acc[OB][27], bacc[OB];
-#pragma unroll
-    for (int u = 0; u < OB; ++u) {
-        bacc[u] = 0.f;
-#pragma unroll
-        for (int tap = 0; tap < 27; ++tap) acc[u][tap] = 0.f;
-    }
-    for (int i = t; i < T::GUARD; i += 256) sx[i] = sx[T::GUARD + NX + i] = 0.f;
-    for (int64_t e = blockIdx.x; e < nelem; e += gridDim.x) {
-        __syncthreads();
-        for (int i = t; i < NX; i += 256) sx[T::GUARD + i] = in[e * NX + i];
-        for (int i = t; i < COUT * T::P; i += 256) sd[i] = dout[e * COUT * T::P + i];
-        __syncthreads();
-        for (int pt = sl; pt < T::P; pt += S::SL) {
-            float mk[27];
-            tap_mask<N>(pt, mk);
-            float g[OB];
-#pragma unroll
-            for (int u = 0; u < OB; ++u) {
-                g[u] = sd[(og * OB + u) * T::P + pt];
-                bacc[u] += g[u];
-            }
-            const float *xc = sx + T::GUARD + c * T::P + pt;
-#pragma unroll
-            for (int tap = 0; tap < 27; ++tap) {
-                const float v = xc[T::off(tap)] * mk[tap];
-#pragma unroll
-                for (int u = 0; u < OB; ++u) acc[u][tap] = fmaf(g[u], v, acc[u][tap]);
-            }
-        }
-    }
-    float *row = partial + ((int64_t)blockIdx.x * S::SL + sl) * S::NT;
-#pragma unroll
-    for (int u = 0; u < OB; ++u) {
-        const int o = og * OB + u;
-#pragma unroll
-        for (int tap = 0; tap < 27; ++tap) row[(o * CIN + c) * 27 + tap] = acc[u][tap];
-        if (c == 0) row[COUT * CIN * 27 + o] = bacc[u];
-    }
-}
-
-// grad[w] += sum over rows of partial[row][w] in two passes, each in a fixed order (FP64
-// accumulation, so the result is reproducible): the rows are cut into kReduceChunks chunks;
-// a workgroup takes 64 columns of one chunk, its four waves summing every fourth row of it
-// and their four sums added in wave order (part2[chunk][w], FP64); then one thread per
-// column adds the chunks in order.  (One thread per column over all rows left most of the
-// GPU idle: a layer has 433-6928 weights, so 2-28 workgroups.)
-constexpr int kReduceChunks = 64;
-
-__global__ __launch_bounds__(256) void k_reduce_chunks(const float *__restrict__ partial, int rows, int nt,
-                                                       double *__restrict__ part2)
-{
-    __shared__ double red[4][64];
-    const int l = threadIdx.x & 63, sl = threadIdx.x >> 6;
-    const int w = blockIdx.x * 64 + l, chunk = blockIdx.y;
-    const int r0 = (int)((int64_t)rows * chunk / kReduceChunks);
-    const int r1 = (int)((int64_t)rows * (chunk + 1) / kReduceChunks);
-    double a = 0.0;
-    if (w < nt)
-        for (int g = r0 + sl; g < r1; g += 4) a += partial[(int64_t)g * nt + w];
-    red[sl][l] = a;
-    __syncthreads();
-    if (sl == 0 && w < nt) part2[(int64_t)chunk * nt + w] = ((red[0][l] + red[1][l]) + red[2][l]) + red[3][l];
-}
-
-__global__ void k_reduce_rows(const double *__restrict__ part2, int nt, float *__restrict__ grad)
-{
-    const int w = blockIdx.x * blockDim.x + threadIdx.x;
-    if (w >= nt) return;
-    double a = 0.0;
-    for (int c = 0; c < kReduceChunks; ++c) a += part2[(int64_t)c * nt + w];
-    grad[w] += (float)a;
-}
-
-template <int N>
-__global__ __launch_bounds__(128) void k_nn_input(int64_t nelem, const double *__restrict__ r,
-                                                  const int32_t *__restrict__ emap, const float *__restrict__ logk,
-                                                  float *__restrict__ x0, float *__restrict__ s_out)
-{
-    constexpr int P = N * N * N;
-    static_assert(P <= 128, "one point per thread");
-    __shared__ double red[128];
-    const int64_t e = blockIdx.x;
-    const int t = threadIdx.x;
-    const double v = t < P ? r[emap[e * P + t]] : 0.0;
-    red[t] = v * v;
-    __syncthreads();
-    for (int h = 64; h > 0; h >>= 1) {
-        if (t < h) red[t] += red[t + h];
-        __syncthreads();
-    }
-    const double rms = sqrt(red[0] / P);
-    const double s = rms > 0.0 ? rms : 1.0;
-    if (t < P) {
-        const float xv = (float)(v / s), lk = logk[e * P + t];
-        x0[(e * 2 + 0) * P + t] = xv;  // tile e: +r
-        x0[(e * 2 + 1) * P + t] = lk;
-        x0[((nelem + e) * 2 + 0) * P + t] = -xv;  // tile nelem + e: -r
-        x0[((nelem + e) * 2 + 1) * P + t] = lk;
-    }
-    if (t == 0) s_out[e] = (float)s;
-}
-
-// z[g] += s_e (out(+r)_e - out(-r)_e) / 2 * inv_mult[g]: the odd part of the network,
-// averaged over the elements sharing g.  out holds the +r tiles, then the -r tiles.
-__global__ void k_nn_output(int64_t total, int P, const float *__restrict__ out, const float *__restrict__ s,
-                            const int32_t *__restrict__ emap, const double *__restrict__ inv_mult, double scale,
-                            double *__restrict__ z)
-{
-    const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (idx >= total) return;
-    const int g = emap[idx];
-    const double odd = 0.5 * scale * ((double)out[idx] - (double)out[total + idx]);
-    unsafeAtomicAdd(z + g, odd * (double)s[idx / P] * inv_mult[g]);
-}
-
-// adjoint: d/d out(+r) = s_e gz inv_mult / 2, d/d out(-r) = its negative
-__global__ void k_nn_output_grad(int64_t total, int P, const double *__restrict__ gz, const float *__restrict__ s,
-                                 const int32_t *__restrict__ emap, const double *__restrict__ inv_mult,
-                                 float *__restrict__ gout)
-{
-    const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (idx >= total) return;
-    const int g = emap[idx];
-    const float v = (float)(0.5 * gz[g] * inv_mult[g] * (double)s[idx / P]);
-    gout[idx] = v;
-    gout[total + idx] = -v;
-}
 
 __global__ void k_count(int64_t total, const int32_t *__restrict__ emap, double *__restrict__ cnt)
 {
@@ -578,6 +335,11 @@ struct Pad {
     {
         return (tap % 3 - 1) + NP * ((tap / 3) % 3 - 1) + NP * NP * (tap / 9 - 1);
     }
+    // the same neighbour in the unpadded tile
+    __host__ __device__ static constexpr int toff(int tap)
+    {
+        return (tap % 3 - 1) + N * ((tap / 3) % 3 - 1) + N * N * (tap / 9 - 1);
+    }
     __device__ static int pad(int pt)
     {
         const int i = pt % N, j = (pt / N) % N, k = pt / (N * N);
@@ -756,7 +518,7 @@ __global__ __launch_bounds__(256, 2) void k_net16(int64_t nelem, const double *_
 #pragma unroll
                 for (int tap = 0; tap < 27; ++tap) {
                     const bool in = (inmask >> tap) & 1u;
-                    const float yv = (float)yb[tap * YP + (in ? tid + Tile<N>::off(tap) : tid)];
+                    const float yv = (float)yb[tap * YP + (in ? tid + T::toff(tap) : tid)];
                     o = in ? o + yv : o;
                 }
                 odd += sgn ? -0.5f * o : 0.5f * o;
@@ -769,91 +531,7 @@ __global__ __launch_bounds__(256, 2) void k_net16(int64_t nelem, const double *_
     }
 }
 
-template <int N>
-hipError_t forward_t(int64_t nelem, const float *params, float *wt, const float *x0, float *a1, float *a2,
-                     float *out, hipStream_t s)
-{
-    using T = Tile<N>;
-    const unsigned nb = (unsigned)((nelem + T::EPB - 1) / T::EPB);
-    float *w1 = wt, *w2 = wt + kNetW1, *w3 = w2 + kNetW2;
-    hipLaunchKernelGGL(k_transpose_w, dim3(nblk(kNetW1)), dim3(256), 0, s, params + kNetOffW1, kNetCh, kNetCin, 0, w1);
-    hipLaunchKernelGGL(k_transpose_w, dim3(nblk(kNetW2)), dim3(256), 0, s, params + kNetOffW2, kNetCh, kNetCh, 0, w2);
-    hipLaunchKernelGGL(k_transpose_w, dim3(nblk(kNetW3)), dim3(256), 0, s, params + kNetOffW3, 1, kNetCh, 0, w3);
-    hipLaunchKernelGGL((k_conv<N, kNetCin, kNetCh, true, false>), dim3(nb), dim3(T::THREADS), 0, s, nelem, x0, w1,
-                       params + kNetOffB1, nullptr, a1);
-    hipLaunchKernelGGL((k_conv<N, kNetCh, kNetCh, true, false>), dim3(nb), dim3(T::THREADS), 0, s, nelem, a1, w2,
-                       params + kNetOffB2, nullptr, a2);
-    hipLaunchKernelGGL((k_conv<N, kNetCh, 1, false, false>), dim3(nb), dim3(T::THREADS), 0, s, nelem, a2, w3,
-                       params + kNetOffB3, nullptr, out);
-    return hipGetLastError();
-}
-
-// floats of the largest block of partial rows (even, so the FP64 chunk sums behind it are
-// 8-byte aligned)
-inline int64_t partial_rows_floats()
-{
-    using L1 = WgradShape<kNetCin, kNetCh>;
-    using L2 = WgradShape<kNetCh, kNetCh>;
-    using L3 = WgradShape<kNetCh, 1>;
-    const int64_t n = (int64_t)kWgradBlocks * std::max({L1::SL * L1::NT, L2::SL * L2::NT, L3::SL * L3::NT});
-    return (n + 1) & ~(int64_t)1;
-}
-
-// grad_w holds the layer's weights followed by its biases: the order of a partial row.
-template <int N, int CIN, int COUT>
-void wgrad_layer(int64_t nelem, const float *in, const float *dout, float *partial, float *grad_w, hipStream_t s)
-{
-    using S = WgradShape<CIN, COUT>;
-    hipLaunchKernelGGL((k_conv_wgrad<N, CIN, COUT>), dim3(kWgradBlocks), dim3(256), 0, s, nelem, in, dout, partial);
-    // the chunk sums go behind the largest partial-row block (nn_partial_floats)
-    double *part2 = reinterpret_cast<double *>(partial + partial_rows_floats());
-    hipLaunchKernelGGL(k_reduce_chunks, dim3((S::NT + 63) / 64, kReduceChunks), dim3(256), 0, s, partial,
-                       kWgradBlocks * S::SL, S::NT, part2);
-    hipLaunchKernelGGL(k_reduce_rows, dim3(nblk(S::NT)), dim3(256), 0, s, part2, S::NT, grad_w);
-}
-
-template <int N>
-hipError_t backward_t(int64_t nelem, const float *params, const float *x0, const float *a1, const float *a2,
-                      const float *gout, float *ga2, float *ga1, float *grads, float *wt, float *partial,
-                      hipStream_t s)
-{
-    using T = Tile<N>;
-    const unsigned nb = (unsigned)((nelem + T::EPB - 1) / T::EPB);
-    // layer 3: weights, then the gradient w.r.t. a2 masked by the ReLU
-    wgrad_layer<N, kNetCh, 1>(nelem, a2, gout, partial, grads + kNetOffW3, s);
-    hipLaunchKernelGGL(k_transpose_w, dim3(nblk(kNetW3)), dim3(256), 0, s, params + kNetOffW3, 1, kNetCh, 1, wt);
-    hipLaunchKernelGGL((k_conv<N, 1, kNetCh, false, true>), dim3(nb), dim3(T::THREADS), 0, s, nelem, gout, wt,
-                       nullptr, a2, ga2);
-    // layer 2
-    wgrad_layer<N, kNetCh, kNetCh>(nelem, a1, ga2, partial, grads + kNetOffW2, s);
-    hipLaunchKernelGGL(k_transpose_w, dim3(nblk(kNetW2)), dim3(256), 0, s, params + kNetOffW2, kNetCh, kNetCh, 1, wt);
-    hipLaunchKernelGGL((k_conv<N, kNetCh, kNetCh, false, true>), dim3(nb), dim3(T::THREADS), 0, s, nelem, ga2, wt,
-                       nullptr, a1, ga1);
-    // layer 1 (the input needs no gradient)
-    wgrad_layer<N, kNetCin, kNetCh>(nelem, x0, ga1, partial, grads + kNetOffW1, s);
-    return hipGetLastError();
-}
-
 }  // namespace
-
-int64_t nn_partial_floats()
-{
-    using L1 = WgradShape<kNetCin, kNetCh>;
-    using L2 = WgradShape<kNetCh, kNetCh>;
-    using L3 = WgradShape<kNetCh, 1>;
-    // partial rows, then the FP64 chunk sums (two floats each)
-    return partial_rows_floats() + 2 * (int64_t)kReduceChunks * std::max({L1::NT, L2::NT, L3::NT});
-}
-
-hipError_t nn_forward(int n, int64_t nelem, const float *params, float *wt, const float *x0, float *a1, float *a2,
-                      float *out, hipStream_t s)
-{
-    if (nelem <= 0) return hipSuccess;
-    if (n == 3) return forward_t<3>(nelem, params, wt, x0, a1, a2, out, s);
-    if (n == 4) return forward_t<4>(nelem, params, wt, x0, a1, a2, out, s);
-    if (n == 5) return forward_t<5>(nelem, params, wt, x0, a1, a2, out, s);
-    return hipErrorInvalidValue;
-}
 
 int64_t nn_pack16_bytes() { return (int64_t)kPackSteps * 64 * sizeof(h4_t); }
 
@@ -869,48 +547,6 @@ hipError_t nn_infer16(int n, int64_t nelem, const float *params, void *wpack, co
     else if (n == 4) hipLaunchKernelGGL(k_net16<4>, dim3(nb), dim3(256), 0, s, nelem, r, emap, logk, wp, params, inv_mult, scale, z);
     else if (n == 5) hipLaunchKernelGGL(k_net16<5>, dim3(nb), dim3(256), 0, s, nelem, r, emap, logk, wp, params, inv_mult, scale, z);
     else return hipErrorInvalidValue;
-    return hipGetLastError();
-}
-
-hipError_t nn_backward(int n, int64_t nelem, const float *params, const float *x0, const float *a1, const float *a2,
-                       const float *gout, float *ga2, float *ga1, float *grads, float *wt, float *partial,
-                       hipStream_t s)
-{
-    if (nelem <= 0) return hipSuccess;
-    if (n == 3) return backward_t<3>(nelem, params, x0, a1, a2, gout, ga2, ga1, grads, wt, partial, s);
-    if (n == 4) return backward_t<4>(nelem, params, x0, a1, a2, gout, ga2, ga1, grads, wt, partial, s);
-    if (n == 5) return backward_t<5>(nelem, params, x0, a1, a2, gout, ga2, ga1, grads, wt, partial, s);
-    return hipErrorInvalidValue;
-}
-
-hipError_t nn_input(int n, int64_t nelem, const double *r, const int32_t *emap, const float *logk, float *x0,
-                    float *s, hipStream_t st)
-{
-    if (nelem <= 0) return hipSuccess;
-    if (n == 3) hipLaunchKernelGGL(k_nn_input<3>, dim3(nelem), dim3(128), 0, st, nelem, r, emap, logk, x0, s);
-    else if (n == 4) hipLaunchKernelGGL(k_nn_input<4>, dim3(nelem), dim3(128), 0, st, nelem, r, emap, logk, x0, s);
-    else if (n == 5) hipLaunchKernelGGL(k_nn_input<5>, dim3(nelem), dim3(128), 0, st, nelem, r, emap, logk, x0, s);
-    else return hipErrorInvalidValue;
-    return hipGetLastError();
-}
-
-hipError_t nn_output(int n, int64_t nelem, const float *out, const float *s, const int32_t *emap,
-                     const double *inv_mult, double scale, double *z, hipStream_t st)
-{
-    const int P = n * n * n;
-    const int64_t tot = nelem * P;
-    if (tot <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_nn_output, dim3(nblk(tot)), dim3(256), 0, st, tot, P, out, s, emap, inv_mult, scale, z);
-    return hipGetLastError();
-}
-
-hipError_t nn_output_grad(int n, int64_t nelem, const double *gz, const float *s, const int32_t *emap,
-                          const double *inv_mult, float *gout, hipStream_t st)
-{
-    const int P = n * n * n;
-    const int64_t tot = nelem * P;
-    if (tot <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_nn_output_grad, dim3(nblk(tot)), dim3(256), 0, st, tot, P, gz, s, emap, inv_mult, gout);
     return hipGetLastError();
 }
 

@@ -144,16 +144,16 @@ int bind(pa_lp *lp, pa_op *op, hipStream_t s)
     lp->ndof = op->ndof;
     lp->box = BoxDims{op->nx, op->ny, op->nz, op->p};
     lp->ness = op->ness;
-    const int64_t P = (int64_t)lp->n * lp->n * lp->n, ne = lp->nelem, nd = lp->ndof;
+    const int64_t P = (int64_t)lp->n * lp->n * lp->n, ne = lp->nelem, nd = lp->ndof, nt = nn_tiles(ne);
     HIP_OK(dalloc(&lp->logk, ne * P));
     HIP_OK(dalloc(&lp->inv_mult, nd));
     HIP_OK(dalloc(&lp->dinv, nd));
-    // network tiles: the +r tile of every element, then the -r tile
-    HIP_OK(dalloc(&lp->x0, 2 * ne * kNetCin * P));
+    // network tiles: the +r and the -r tile of every element
+    HIP_OK(dalloc(&lp->x0, nt * kNetCin * P));
     HIP_OK(dalloc(&lp->s, ne));
-    HIP_OK(dalloc(&lp->a1, 2 * ne * kNetCh * P));
-    HIP_OK(dalloc(&lp->a2, 2 * ne * kNetCh * P));
-    HIP_OK(dalloc(&lp->out, 2 * ne * P));
+    HIP_OK(dalloc(&lp->a1, nt * kNetCh * P));
+    HIP_OK(dalloc(&lp->a2, nt * kNetCh * P));
+    HIP_OK(dalloc(&lp->out, nt * P));
     HIP_OK(dalloc(&lp->v0, nd));
     HIP_OK(dalloc(&lp->v1, nd));
     HIP_OK(dalloc(&lp->v2, nd));
@@ -252,10 +252,10 @@ int bind(pa_lp *lp, pa_op *op, hipStream_t s)
 
 int ensure_training(pa_lp *lp)
 {
-    const int64_t P = (int64_t)lp->n * lp->n * lp->n;
-    if (!lp->ga1) HIP_OK(dalloc(&lp->ga1, 2 * lp->nelem * kNetCh * P));
-    if (!lp->ga2) HIP_OK(dalloc(&lp->ga2, 2 * lp->nelem * kNetCh * P));
-    if (!lp->gout) HIP_OK(dalloc(&lp->gout, 2 * lp->nelem * P));
+    const int64_t P = (int64_t)lp->n * lp->n * lp->n, nt = nn_tiles(lp->nelem);
+    if (!lp->ga1) HIP_OK(dalloc(&lp->ga1, nt * kNetCh * P));
+    if (!lp->ga2) HIP_OK(dalloc(&lp->ga2, nt * kNetCh * P));
+    if (!lp->gout) HIP_OK(dalloc(&lp->gout, nt * P));
     if (!lp->partial) HIP_OK(dalloc(&lp->partial, (size_t)nn_partial_floats()));
     if (!lp->tr_r) HIP_OK(dalloc(&lp->tr_r, lp->ndof));
     if (!lp->tr_t) HIP_OK(dalloc(&lp->tr_t, lp->ndof));
@@ -274,7 +274,7 @@ int net_part(pa_lp *lp, const double *r, double *z, hipStream_t s, bool fp16, bo
                           z, s));
     } else {
         HIP_OK(nn_input(lp->n, lp->nelem, r, op->d_elem_dofs, lp->logk, lp->x0, lp->s, s));
-        HIP_OK(nn_forward(lp->n, 2 * lp->nelem, lp->params, lp->wt, lp->x0, lp->a1, lp->a2, lp->out, s));
+        HIP_OK(nn_forward(lp->n, lp->nelem, lp->params, lp->wt, lp->x0, lp->a1, lp->a2, lp->out, s));
         HIP_OK(nn_output(lp->n, lp->nelem, lp->out, lp->s, op->d_elem_dofs, lp->inv_mult, scale, z, s));
     }
     if (op->ness) HIP_OK(vec_zero_list(z, op->d_ess, op->ness, s));
@@ -341,8 +341,8 @@ int loss_grad(pa_lp *lp, const double *r, const double *t, hipStream_t s)
     if (op->ness) HIP_OK(vec_zero_list(gz, op->d_ess, op->ness, s));
     HIP_OK(nn_output_grad(lp->n, lp->nelem, gz, lp->s, op->d_elem_dofs, lp->inv_mult, lp->gout, s));
     HIP_OK(vec_fill_f32(lp->grads, 0.0f, kNetParams, s));
-    HIP_OK(nn_backward(lp->n, 2 * lp->nelem, lp->params, lp->x0, lp->a1, lp->a2, lp->gout, lp->ga2, lp->ga1,
-                       lp->grads, lp->wt, lp->partial, s));
+    HIP_OK(nn_backward(lp->n, lp->nelem, lp->wt, lp->x0, lp->a1, lp->a2, lp->gout, lp->ga2, lp->ga1, lp->grads,
+                       lp->partial, s));
     return PA_OK;
 }
 
@@ -365,7 +365,7 @@ extern "C" int pa_lp_create(pa_op *op, const pa_lp_opts *o, pa_lp **out)
     HIP_OK(dalloc(&lp->grads, kNetParams));
     HIP_OK(dalloc(&lp->adam_m, kNetParams));
     HIP_OK(dalloc(&lp->adam_v, kNetParams));
-    HIP_OK(dalloc(&lp->wt, kNetW1 + kNetW2 + kNetW3));
+    HIP_OK(dalloc(&lp->wt, kNetPack32));
     HIP_OK(dalloc(&lp->red, 2 * kRedBlocks));
     HIP_OK(dalloc(&lp->dsc, 4));
     HIP_OK(hipMalloc(&lp->wpack, (size_t)nn_pack16_bytes()));
