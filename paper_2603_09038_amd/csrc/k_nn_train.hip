@@ -371,7 +371,7 @@ __global__ __launch_bounds__(256, 4) void k_conv_out(int64_t ngroups, const floa
 // 27 taps' blocks stay in registers over every row a wave takes; the waves of a workgroup
 // are then added in wave order through LDS and the workgroup writes one row of `partial`
 // (weights, then biases), which the two reduction kernels add in a fixed order.
-// Layer 2, 32^3, p = 4: 2.46 -> 0.71 ms (the matrix pipe, as the convolutions).
+// Layer 2, 32^3, p = 4: 2.46 -> 0.70 ms (the matrix pipe, as the convolutions).
 // The rows come as 16-byte loads (a vector memory instruction occupies the CU's address unit
 // for about 16 cycles whatever its width: with 4-byte loads in the layout the MFMA wants this
 // kernel took 1.02-1.22 ms) and are turned through wave-private LDS, a point's block at
@@ -388,13 +388,17 @@ template <int N, int PITCH>
 __device__ __forceinline__ void turn_row(f4_t (&b)[N], const f4_t (&raw)[N], float *buf, int lane)
 {
     constexpr int PT = kTileGroup * PITCH;
-#pragma unroll
-    for (int i = 0; i < N; ++i) *reinterpret_cast<f4_t *>(buf + i * PT + (lane >> 2) * PITCH + (lane & 3) * 4) = raw[i];
+    // the wave's lanes run in lockstep and the LDS serves a wave in order: only the compiler has
+    // to keep the reads behind the other lanes' writes, and those behind the row before
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront", "local");
     const float *p = buf + (lane & 15) + (lane >> 4) * (PITCH == 16 ? PITCH : 4 * PITCH);
 #pragma unroll
-    for (int i = 0; i < N; ++i)
+    for (int i = 0; i < N; ++i) {
+        *reinterpret_cast<f4_t *>(buf + i * PT + (lane >> 2) * PITCH + (lane & 3) * 4) = raw[i];
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront", "local");
 #pragma unroll
         for (int s = 0; s < 4; ++s) b[i][s] = p[i * PT + s * (PITCH == 16 ? 4 * PITCH : PITCH)];
+    }
 }
 
 template <int N>
@@ -440,19 +444,19 @@ __global__ __launch_bounds__(256, 2) void k_wgrad16(int64_t ngroups, const float
         // input row jp meets the output rows jp + 1, jp, jp - 1 (ty = 0, 1, 2): three output
         // rows in a ring of slots, the input row double-buffered; the loads of the next rows
         // are in flight during this row's MFMAs
-        f4_t a[3][N], b[N], ra[N], rb[N];
+        f4_t a[3][N], b[N], ra[2][N], rb[2][N];
         const int64_t rin = (g * N + kin) * N, rout = (g * N + k) * N;
-        load_raw<N>(rb, in, rin, lane);
-        load_raw<N>(ra, dout, rout, lane);
-        turn_row<N, 16>(b, rb, buf, lane);
-        load_raw<N>(rb, dout, rout + 1, lane);
-        turn_row<N, 16>(a[0], ra, buf, lane);
-        turn_row<N, 16>(a[1], rb, buf, lane);
+        load_raw<N>(rb[0], in, rin, lane);
+        load_raw<N>(ra[0], dout, rout, lane);
+        load_raw<N>(ra[1], dout, rout + 1, lane);
+        load_raw<N>(rb[1], in, rin + 1, lane);
+        turn_row<N, 16>(b, rb[0], buf, lane);
+        turn_row<N, 16>(a[0], ra[0], buf, lane);
+        load_raw<N>(ra[0], dout, rout + 2, lane);
+        turn_row<N, 16>(a[1], ra[1], buf, lane);
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int jp = 0; jp < N; ++jp) {
-            if (jp + 1 < N) load_raw<N>(rb, in, rin + jp + 1, lane);
-            if (jp + 2 < N) load_raw<N>(ra, dout, rout + jp + 2, lane);
-            __builtin_amdgcn_sched_barrier(0);
             if (jp > 0) block(a[(jp + 2) % 3], b, acc + 6);
             block(a[jp % 3], b, acc + 3);
             if (jp + 1 < N) block(a[(jp + 1) % 3], b, acc);
@@ -462,9 +466,12 @@ __global__ __launch_bounds__(256, 2) void k_wgrad16(int64_t ngroups, const float
                     const f4_t v = a[jp % 3][i];
                     bacc += (v[0] + v[1]) + (v[2] + v[3]);
                 }
+            // the rows after the next: requested before the next ones are turned
+            if (jp + 2 < N) load_raw<N>(rb[jp & 1], in, rin + jp + 2, lane);
+            if (jp + 3 < N) load_raw<N>(ra[(jp + 1) & 1], dout, rout + jp + 3, lane);
             __builtin_amdgcn_sched_barrier(0);
-            if (jp + 1 < N) turn_row<N, 16>(b, rb, buf, lane);
-            if (jp + 2 < N) turn_row<N, 16>(a[(jp + 2) % 3], ra, buf, lane);
+            if (jp + 1 < N) turn_row<N, 16>(b, rb[(jp + 1) & 1], buf, lane);
+            if (jp + 2 < N) turn_row<N, 16>(a[(jp + 2) % 3], ra[jp & 1], buf, lane);
         }
     }
     __syncthreads();
