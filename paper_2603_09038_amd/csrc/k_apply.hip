@@ -11,6 +11,7 @@
 #include <type_traits>
 
 #include "apply_passes.h"
+#include "apply_chain.h"
 #include "geometry.h"
 
 namespace hexpa {
@@ -453,6 +454,8 @@ __global__ __launch_bounds__(256) void k_dstep(int64_t npts, const T *__restrict
 //   forward passes | wait, D-step | issue D(g+1) | transposed passes and scatter.
 // So the D stream of the next group overlaps the transposed passes and the forward
 // passes, and the gathers overlap the forward passes, without holding registers.
+// (FP64 with MFMA contractions runs the chained kernel at these orders; this one serves the
+// vector-ALU and the 16-bit executors, and the mass operator at p = 4.)
 constexpr int kDmaMinD = 6;                // orders p >= 5 (measured faster there; diffusion at p <= 4 keeps the register kernel)
 constexpr int kDmaLdsBudget = 53 * 1024;   // LDS bytes per workgroup of the DMA kernel
 
@@ -761,9 +764,10 @@ static hipError_t launch_mf(const pa_op *op, const double *x, double *y, hipStre
     return hipGetLastError();
 }
 
+// the kernels that work on groups of elements, pass by pass
 template <int D, int Q, int OPS, int EX, bool ATOMIC>
-static hipError_t launch_k(const pa_op *op, const typename ExT<EX>::T *qd, const typename ExT<EX>::T *x,
-                           typename ExT<EX>::T *y, const int32_t *elist, int n, hipStream_t s)
+static hipError_t launch_groups(const pa_op *op, const typename ExT<EX>::T *qd, const typename ExT<EX>::T *x,
+                                typename ExT<EX>::T *y, const int32_t *elist, int n, hipStream_t s)
 {
     using T = typename ExT<EX>::T;
     using CFG = ApplyCfg<D, Q, OPS, EX>;
@@ -785,6 +789,24 @@ static hipError_t launch_k(const pa_op *op, const typename ExT<EX>::T *qd, const
                            y);
     }
     return hipGetLastError();
+}
+
+template <int D, int Q, int OPS, int EX, bool ATOMIC>
+static hipError_t launch_k(const pa_op *op, const typename ExT<EX>::T *qd, const typename ExT<EX>::T *x,
+                           typename ExT<EX>::T *y, const int32_t *elist, int n, hipStream_t s)
+{
+    if constexpr (EX == EX_MFMA64 && ChainShape<D, Q, OPS>::ok) {  // FP64 MFMA at p >= 5
+        if (n == 0) return hipSuccess;
+        constexpr auto kern = k_apply_chain<D, Q, OPS, ATOMIC>;
+        constexpr int NT = ChainShape<D, Q, OPS>::NT, RUN = ChainShape<D, Q, OPS>::RUN;
+        // runs as long as leaves every resident workgroup a few
+        const int cap = capped(op, persistent_blocks<kern>(NT, n)), run = std::max(1, std::min(RUN, n / (2 * cap)));
+        hipLaunchKernelGGL(kern, dim3(std::min(cap, (n + run - 1) / run)), dim3(NT), 0, s, n, run, elist,
+                           op->d_elem_dofs, qd, op->d_tab, x, y);
+        return hipGetLastError();
+    } else {
+        return launch_groups<D, Q, OPS, EX, ATOMIC>(op, qd, x, y, elist, n, s);
+    }
 }
 
 template <int D, int Q, int OPS>
@@ -860,6 +882,11 @@ static void group_shape(int *elems, int *threads)
 {
     using T = typename ExT<EX>::T;
     using CFG = ApplyCfg<D, Q, OPS, EX, FUSED_STORED ? 0 : 1>;
+    if constexpr (FUSED_STORED && EX == EX_MFMA64 && ChainShape<D, Q, OPS>::ok) {
+        *elems = 1;
+        *threads = ChainShape<D, Q, OPS>::NT;
+        return;
+    }
     constexpr bool DMA = FUSED_STORED && DmaShape<D, Q, OPS, T>::ok;
     *elems = DMA ? DmaShape<D, Q, OPS, T>::E : Shape<D, Q, OPS, (int)sizeof(T), CFG::NT, CFG::BUDGET>::E;
     *threads = DMA ? DmaShape<D, Q, OPS, T>::NT : CFG::NT;
