@@ -525,11 +525,12 @@ struct PcgWork {
     }
 };
 
-// Runs step(it) for it = 1, 2, ... from an initialised state (hist[0] = r0.r0 read back
-// as rr0); each step records hist[2 it] = r.r and hist[2 it + 1] = breakdown flag.  Stops
-// when r.r <= tol2, on breakdown, or after max_it.  The host inspects the residual of the
-// previous check while the next iteration is already queued, so the device never idles
-// waiting for the host.
+// Runs step(it, slot) for it = 1, 2, ... from an initialised state (hist[0] = r0.r0 read back
+// as rr0); each step records hist[2 it] = r.r and hist[2 it + 1] = breakdown flag, and where
+// slot is not null its kernel writes the two there, into pinned host memory.  Stops when
+// r.r <= tol2, on breakdown, or after max_it.  The host inspects the residual of the previous
+// check while the next iteration is already queued, so the device never idles waiting for the
+// host; a slot is written again only after the host has read it.
 template <class T, class StepF>
 int lagged_iterate(StepF step, double tol2, int max_it, int check, PcgWork<T> &w, hipStream_t s, double rr0,
                    int *iters, double *rr_out)
@@ -540,12 +541,11 @@ int lagged_iterate(StepF step, double tol2, int max_it, int check, PcgWork<T> &w
     int pending = -1, nchecks = 0;
     while (status == PA_ERR_NOT_CONVERGED && it < max_it) {
         ++it;
-        int rc = step(it);
+        const bool look = it % check == 0 || it == max_it;
+        const int slot = look ? (nchecks++) & 1 : 0;
+        int rc = step(it, look ? w.h_hist + 2 * slot : nullptr);
         if (rc) return rc;
-        if (it % check == 0 || it == max_it) {
-            const int slot = (nchecks++) & 1;
-            HIP_OK(hipMemcpyAsync(w.h_hist + 2 * slot, w.hist + 2 * (size_t)it, 2 * sizeof(double),
-                                  hipMemcpyDeviceToHost, s));
+        if (look) {
             HIP_OK(hipEventRecord(w.ev[slot], s));
             if (pending >= 0) {
                 HIP_OK(hipEventSynchronize(w.ev[pending]));
@@ -574,17 +574,18 @@ struct NoHook {
 // (P)CG iterations (Saad, Alg. 9.1) with Jacobi dinv (nullptr: none) from the state cg_init
 // left in w; after(it) runs once iteration it has been enqueued.  apply(p, Ap) must add A p
 // into Ap, which holds zeros on entry (the direction update clears it for the next one).
+// masked: dinv is zero on the essential DOFs, and what apply leaves there does not matter.
 template <class T, class ApplyF, class AfterF = NoHook>
-int pcg_iterate(ApplyF apply, T *x, const T *dinv, int64_t n, double tol2, int max_it, int check, PcgWork<T> &w,
+int pcg_iterate(ApplyF apply, T *x, const T *dinv, bool masked, int64_t n, double tol2, int max_it, int check, PcgWork<T> &w,
                 hipStream_t s, double rr0, int *iters, double *rr_out, AfterF after = AfterF())
 {
     HIP_OK(vec_fill(w.Ap, T(0), n, s));
-    auto step = [&](int it) -> int {
+    auto step = [&](int it, double *slot) -> int {
         int rc = apply(w.p, w.Ap);
         if (rc) return rc;
         HIP_OK(cg_pap<T>(w.p, w.Ap, n, w.partial2, s));
-        HIP_OK(cg_update_xr<T>(x, w.r, w.p, w.Ap, dinv, n, w.partial2, w.partial, w.sc, s));
-        HIP_OK(cg_update_dir<T>(w.p, w.r, dinv, w.Ap, n, w.partial, w.sc, w.hist, it, 1.0, s));
+        HIP_OK(cg_update_xr<T>(nullptr, w.r, w.p, w.Ap, dinv, masked, n, w.partial2, w.partial, w.sc, s));
+        HIP_OK(cg_update_dir<T>(x, w.p, w.r, dinv, w.Ap, n, w.partial, w.sc, w.hist, it, 1.0, slot, s));
         return after(it);
     };
     return lagged_iterate<T>(step, tol2, max_it, check, w, s, rr0, iters, rr_out);
@@ -636,10 +637,7 @@ static int solve_mixed_ir(pa_op *op, const double *b, double *x, const pa_cg_opt
     }
     std::unique_ptr<void, void (*)(void *)> g2(dinv32, dfree);
     auto apply32 = [&](const float *p, float *y) -> int {
-        int r2 = do_apply_lp(op, p, y, fmt, s, false);
-        if (r2) return r2;
-        if (con && op->ness) HIP_OK(vec_set_list(y, 0.0f, op->d_ess, op->ness, s));
-        return PA_OK;
+        return do_apply_lp(op, p, y, fmt, s, false);
     };
     auto t0 = std::chrono::steady_clock::now();
     int status = PA_ERR_NOT_CONVERGED, outer = 0, inner_total = 0;
@@ -671,7 +669,7 @@ static int solve_mixed_ir(pa_op *op, const double *b, double *x, const pa_cg_opt
         const double rr0 = w32.h_hist[0];
         int it_in = 0;
         double rr_in = 0.0;
-        int st = pcg_iterate<float>(apply32, d32, dinv32, n, inner_rtol * inner_rtol * rr0, inner_max, check, w32, s,
+        int st = pcg_iterate<float>(apply32, d32, dinv32, con && op->ness, n, inner_rtol * inner_rtol * rr0, inner_max, check, w32, s,
                                     rr0, &it_in, &rr_in);
         inner_total += it_in;
         if (st == PA_ERR_BREAKDOWN && it_in <= 1) { status = PA_ERR_BREAKDOWN; break; }
@@ -732,11 +730,11 @@ static int solve_fcg(pa_op *op, const double *b, double *x, const pa_cg_opts *o,
         return PA_OK;
     };
     if ((rc = capture(0))) return rc;
-    auto step = [&](int it) -> int {
+    auto step = [&](int it, double *slot) -> int {
         int r2 = cg_apply(op, con, w.p, w.Ap, s);
         if (r2) return r2;
         HIP_OK(cg_alpha<double>(w.p, w.Ap, n, w.partial, w.sc, s));
-        HIP_OK(fcg_update(x, w.r, rold, w.p, w.Ap, n, w.partial, w.sc, w.hist, it, s));
+        HIP_OK(fcg_update(x, w.r, rold, w.p, w.Ap, n, w.partial, w.sc, w.hist, it, slot, s));
         if ((r2 = capture(it))) return r2;
         r2 = lp_precondition(lp, w.r, z, s);
         if (r2) return r2;
@@ -757,8 +755,8 @@ static int solve_fcg(pa_op *op, const double *b, double *x, const pa_cg_opts *o,
         HIP_OK(hipMemcpyAsync(w.h_hist, w.hist, sizeof(double), hipMemcpyDeviceToHost, s));
         HIP_OK(hipStreamSynchronize(s));
         int it2 = 0;
-        auto apply64 = [&](const double *p, double *y) { return cg_apply(op, con, p, y, s, false); };
-        status = pcg_iterate<double>(apply64, x, dinv, n, tol2, o->max_it - it, check, w, s, w.h_hist[0], &it2, &rr);
+        auto apply64 = [&](const double *p, double *y) { return do_apply(op, op->variant, p, y, s, false); };
+        status = pcg_iterate<double>(apply64, x, dinv, con && op->ness, n, tol2, o->max_it - it, check, w, s, w.h_hist[0], &it2, &rr);
         if (status != PA_OK && status != PA_ERR_NOT_CONVERGED && status != PA_ERR_BREAKDOWN) return status;
         it += it2;
     }
@@ -791,6 +789,7 @@ static int solve_mixed_ru(pa_op *op, const double *b, double *x, const pa_cg_opt
     const int fmt = o->lp_fmt;
     if (fmt != PA_LP_FP16 && fmt != PA_LP_BF16) return arg_error("cg_solve: lp_fmt must be PA_LP_FP16 or PA_LP_BF16");
     if (!dinv64) return arg_error("cg_solve: MIXED_RU needs the Jacobi diagonal");
+    const bool masked = con && op->ness;  // cg_solve zeroed dinv on the essential DOFs
     const int kmax = o->inner_max > 0 ? o->inner_max : 100;
     const int max_total = o->max_it;
     int rc = ensure_qdata32(op, s);
@@ -825,6 +824,7 @@ static int solve_mixed_ru(pa_op *op, const double *b, double *x, const pa_cg_opt
         std::frexp(rmax, &ex);
         return std::ldexp(1.0, -ex);
     };
+    HIP_OK(vec_fill(w32.p, 0.0f, n, s));  // the first direction is z + 0 p: p must be finite
     auto t0 = std::chrono::steady_clock::now();
     int status = PA_ERR_NOT_CONVERGED, total = 0, replacements = 0;
     double rel = 0.0, rmax = 0.0;
@@ -843,7 +843,8 @@ static int solve_mixed_ru(pa_op *op, const double *b, double *x, const pa_cg_opt
         HIP_OK(vec_to_f32(w32.r, w64.Ap, ns, n, s));
         HIP_OK(vec_fill(xh, 0.0f, n, s));
         HIP_OK(cg_rz_partials<float>(w32.r, dinv32, n, w32.partial, s));
-        HIP_OK(cg_update_dir<float>(w32.p, w32.r, dinv32, w32.Ap, n, w32.partial, w32.sc, w32.hist, total, f, s));
+        HIP_OK(cg_update_dir<float>(nullptr, w32.p, w32.r, dinv32, w32.Ap, n, w32.partial, w32.sc, w32.hist, total, f,
+                                    nullptr, s));
         scale = ns;
         first = false;
         // chunk length from the observed rate (iterations per factor of reduction)
@@ -856,12 +857,13 @@ static int solve_mixed_ru(pa_op *op, const double *b, double *x, const pa_cg_opt
         for (int j = 1; j <= k; ++j) {
             rc = do_apply_lp(op, w32.p, w32.Ap, fmt, s, false);
             if (rc) return rc;
-            if (con && op->ness) HIP_OK(vec_set_list(w32.Ap, 0.0f, op->d_ess, op->ness, s));
             HIP_OK(cg_pap<float>(w32.p, w32.Ap, n, w32.partial2, s));
-            HIP_OK(cg_update_xr<float>(xh, w32.r, w32.p, w32.Ap, dinv32, n, w32.partial2, w32.partial, w32.sc, s));
+            // the chunk's last iteration has no direction update: x moves with the residual
+            HIP_OK(cg_update_xr<float>(j < k ? nullptr : xh, w32.r, w32.p, w32.Ap, dinv32, masked, n, w32.partial2,
+                                       w32.partial, w32.sc, s));
             if (j < k)
-                HIP_OK(cg_update_dir<float>(w32.p, w32.r, dinv32, w32.Ap, n, w32.partial, w32.sc, w32.hist, total + j,
-                                            1.0, s));
+                HIP_OK(cg_update_dir<float>(xh, w32.p, w32.r, dinv32, w32.Ap, n, w32.partial, w32.sc, w32.hist,
+                                            total + j, 1.0, nullptr, s));
         }
         total += k;
         HIP_OK(vec_axpy_f32(x, 1.0 / scale, xh, n, s));
@@ -918,10 +920,7 @@ static int solve_mixed_fcg(pa_op *op, const double *b, double *x, const pa_cg_op
     std::unique_ptr<void, void (*)(void *)> g5(tmp, dfree);
     HIP_OK(vec_to_f32(dinv32, dinv64, 1.0, n, s));
     auto apply32 = [&](const float *p, float *y) -> int {
-        int r2 = do_apply_lp(op, p, y, fmt, s, false);
-        if (r2) return r2;
-        if (con && op->ness) HIP_OK(vec_set_list(y, 0.0f, op->d_ess, op->ness, s));
-        return PA_OK;
+        return do_apply_lp(op, p, y, fmt, s, false);
     };
     int inner_total = 0;
     double *hbuf = w32.h_hist;  // pinned scratch for the scale read-back (slots 2, 3 are free here)
@@ -943,7 +942,7 @@ static int solve_mixed_fcg(pa_op *op, const double *b, double *x, const pa_cg_op
         const double rr0 = hbuf[0];
         int it_in = 0;
         double rr_in = 0.0;
-        int st = pcg_iterate<float>(apply32, d32, dinv32, n, inner_rtol * inner_rtol * rr0, inner_max, check, w32, s,
+        int st = pcg_iterate<float>(apply32, d32, dinv32, con && op->ness, n, inner_rtol * inner_rtol * rr0, inner_max, check, w32, s,
                                     rr0, &it_in, &rr_in);
         inner_total += it_in;
         if (st != PA_OK && st != PA_ERR_NOT_CONVERGED && st != PA_ERR_BREAKDOWN) return st;
@@ -972,7 +971,7 @@ static int solve_mixed_fcg(pa_op *op, const double *b, double *x, const pa_cg_op
             rc = cg_apply(op, con, w.p, w.Ap, s);
             if (rc) return rc;
             HIP_OK(cg_alpha<double>(w.p, w.Ap, n, w.partial, w.sc, s));
-            HIP_OK(fcg_update(x, w.r, rold, w.p, w.Ap, n, w.partial, w.sc, w.hist, it, s));
+            HIP_OK(fcg_update(x, w.r, rold, w.p, w.Ap, n, w.partial, w.sc, w.hist, it, nullptr, s));
             HIP_OK(hipMemcpyAsync(w.h_hist, w.hist + 2 * (size_t)it, 2 * sizeof(double), hipMemcpyDeviceToHost, s));
             HIP_OK(hipStreamSynchronize(s));
             rr = w.h_hist[0];
@@ -1032,6 +1031,9 @@ extern "C" int cg_solve(pa_op *op, const double *b, double *x, const pa_cg_opts 
         int rc = pa_diag(op, dinv, con ? 1 : 0, s);
         if (rc) return rc;
         HIP_OK(vec_recip(dinv, dinv, n, s));
+        // zero on the essential DOFs (r, z and p vanish there): the update kernels then know them
+        // and leave r alone, whatever the apply puts into Ap
+        if (con && op->ness) HIP_OK(vec_zero_list(dinv, op->d_ess, op->ness, s));
     }
     if (con && op->ness) HIP_OK(vec_copy_list(x, b, op->d_ess, op->ness, s));
     HIP_OK(vec_dot<double>(b, b, n, w.partial, w.tmp, s));
@@ -1060,7 +1062,8 @@ extern "C" int cg_solve(pa_op *op, const double *b, double *x, const pa_cg_opts 
     auto t0 = std::chrono::steady_clock::now();
     int it = 0;
     double rr = 0.0;
-    auto apply64 = [&](const double *p, double *y) { return cg_apply(op, con, p, y, s, false); };
+    const bool masked = dinv && con && op->ness;  // without Jacobi the apply clears the essential entries
+    auto apply64 = [&](const double *p, double *y) { return cg_apply(op, con && !masked, p, y, s, false); };
     // iterates requested by the caller (training-data capture)
     int cap = 0;
     auto capture = [&](int k) -> int {
@@ -1072,7 +1075,7 @@ extern "C" int cg_solve(pa_op *op, const double *b, double *x, const pa_cg_opts 
     };
     if ((rc = capture(0))) return rc;
     const int status =
-        pcg_iterate<double>(apply64, x, dinv, n, tol2, o->max_it, check, w, s, w.h_hist[0], &it, &rr, capture);
+        pcg_iterate<double>(apply64, x, dinv, masked, n, tol2, o->max_it, check, w, s, w.h_hist[0], &it, &rr, capture);
     if (status != PA_OK && status != PA_ERR_NOT_CONVERGED && status != PA_ERR_BREAKDOWN) return status;
     auto t1 = std::chrono::steady_clock::now();
     res->seconds = std::chrono::duration<double>(t1 - t0).count();

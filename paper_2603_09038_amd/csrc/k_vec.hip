@@ -3,6 +3,8 @@
 // count and a fixed tree order, so sums are bitwise reproducible.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+
 #include "k_vec.h"
 
 namespace hexpa {
@@ -14,6 +16,10 @@ constexpr int kUnroll = 4;
 namespace {
 
 inline unsigned nblk(int64_t n) { return (unsigned)((n + 255) / 256); }
+// blocks of a reduction over n entries: two entries a thread until the grid is full (every
+// block adds up all partial sums of the reduction before it, which for small n took longer
+// than the update itself with 1024 of them).  A function of n alone: reproducible sums.
+inline unsigned red_blocks(int64_t n) { return (unsigned)std::max<int64_t>(1, std::min<int64_t>(kRedBlocks, (n + 511) / 512)); }
 
 template <class T>
 __global__ void k_fill(T *y, T v, int64_t n)
@@ -36,28 +42,28 @@ __global__ void k_copy_list(double *y, const double *x, const int32_t *list, int
     if (i < n) y[list[i]] = x[list[i]];
 }
 
-// Block-wide sum of NV values per thread in a fixed tree order.
+// Block-wide sum of NV values per thread in a fixed order (256 threads): a shuffle tree in each
+// wave, then the four wave sums in wave order; every thread gets the sums.  sh: NV x 4 doubles.
+// One barrier instead of the nine of a tree through LDS.
 template <int NV>
-__device__ inline void block_sum(double (&v)[NV], double *sh /*[NV][256]*/)
+__device__ inline void block_sum(double (&v)[NV], double *sh)
 {
     const int t = threadIdx.x;
 #pragma unroll
-    for (int k = 0; k < NV; ++k) sh[k * 256 + t] = v[k];
-    __syncthreads();
-    for (int s = 128; s > 0; s >>= 1) {
-        if (t < s)
+    for (int k = 0; k < NV; ++k) {
 #pragma unroll
-            for (int k = 0; k < NV; ++k) sh[k * 256 + t] += sh[k * 256 + t + s];
-        __syncthreads();
+        for (int o = 32; o > 0; o >>= 1) v[k] += __shfl_xor(v[k], o);
+        if ((t & 63) == 0) sh[4 * k + (t >> 6)] = v[k];
     }
+    __syncthreads();
 #pragma unroll
-    for (int k = 0; k < NV; ++k) v[k] = sh[k * 256];
+    for (int k = 0; k < NV; ++k) v[k] = (sh[4 * k] + sh[4 * k + 1]) + (sh[4 * k + 2] + sh[4 * k + 3]);
 }
 
 template <class T>
 __global__ void k_dot_partial(const T *__restrict__ x, const T *__restrict__ y, int64_t n, double *partial)
 {
-    __shared__ double sh[256];
+    __shared__ double sh[4];
     double v[1] = {0.0};
     const int64_t st = (int64_t)gridDim.x * blockDim.x;
     int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -107,7 +113,7 @@ __global__ void k_max_to(const double *partial, int nb, double *out)
 
 __global__ void k_reduce_to(const double *partial, int nb, int stride, double *out)
 {
-    __shared__ double sh[256];
+    __shared__ double sh[4];
     double v[1] = {0.0};
     for (int i = threadIdx.x; i < nb; i += 256) v[0] += partial[i * stride];
     block_sum<1>(v, sh);
@@ -117,7 +123,7 @@ __global__ void k_reduce_to(const double *partial, int nb, int stride, double *o
 // alpha = rz / pAp from the partial sums of p.Ap; flags breakdown.
 __global__ void k_cg_alpha(const double *partial, int nb, CgScalars *s)
 {
-    __shared__ double sh[256];
+    __shared__ double sh[4];
     double v[1] = {0.0};
     for (int i = threadIdx.x; i < nb; i += 256) v[0] += partial[i];
     block_sum<1>(v, sh);
@@ -134,14 +140,17 @@ __global__ void k_cg_alpha(const double *partial, int nb, CgScalars *s)
 }
 
 // alpha = rz / (p . Ap) from the partial sums of p . Ap, formed identically (same order) in
-// every block; x += alpha p; r -= alpha Ap; rz_prev = rz; partial sums of (r . dinv r) and
-// (r . r) into rz_part.
-template <class T>
-__global__ void k_cg_update1(T *__restrict__ x, T *__restrict__ r, const T *__restrict__ p, const T *__restrict__ Ap,
-                             const T *__restrict__ dinv, int64_t n, CgScalars *__restrict__ s,
-                             const double *__restrict__ pap_part, int nb, double *__restrict__ rz_part)
+// every block; r -= alpha Ap; with WITHX also x += alpha p (otherwise the direction update,
+// which reads p anyway, does that); rz_prev = rz; partial sums of (r . dinv r) and (r . r) into
+// rz_part.  MASKED: dinv is zero on the essential DOFs and r keeps its (zero) value there, so
+// Ap need not be cleared on them first.
+template <class T, bool WITHX, bool MASKED>
+__global__ __launch_bounds__(256) void k_cg_update1(T *__restrict__ x, T *__restrict__ r, const T *__restrict__ p,
+                                                    const T *__restrict__ Ap, const T *__restrict__ dinv, int64_t n,
+                                                    CgScalars *__restrict__ s, const double *__restrict__ pap_part,
+                                                    int nb, double *__restrict__ rz_part)
 {
-    __shared__ double sh[2 * 256];
+    __shared__ double sh[12];
     double a[1] = {0.0};
     for (int i = threadIdx.x; i < nb; i += 256) a[0] += pap_part[i];
     block_sum<1>(a, sh);
@@ -156,14 +165,14 @@ __global__ void k_cg_update1(T *__restrict__ x, T *__restrict__ r, const T *__re
         s->pAp = pAp;
         s->alpha = alpha;
         s->rz_prev = rz;
+        s->frozen = frozen;
         if (bad) s->breakdown = 1;
     }
-    __syncthreads();  // sh is reused below
     double v[2] = {0.0, 0.0};
     auto one = [&](int64_t i, T pi, T xi, T ai, T r0, T di) {
         T ri = r0;
-        if (!frozen) {
-            x[i] = (T)fma(alpha, (double)pi, (double)xi);
+        if (!frozen && !(MASKED && di == T(0))) {
+            if (WITHX) x[i] = (T)fma(alpha, (double)pi, (double)xi);
             ri = (T)fma(-alpha, (double)ai, (double)r0);
             r[i] = ri;
         }
@@ -178,8 +187,8 @@ __global__ void k_cg_update1(T *__restrict__ x, T *__restrict__ r, const T *__re
 #pragma unroll
         for (int u = 0; u < kUnroll; ++u) {
             const int64_t j = i + u * st;
-            pv[u] = p[j];
-            xv[u] = x[j];
+            pv[u] = WITHX ? p[j] : T(0);
+            xv[u] = WITHX ? x[j] : T(0);
             av[u] = Ap[j];
             rv[u] = r[j];
             dv[u] = dinv ? dinv[j] : T(1);
@@ -187,8 +196,8 @@ __global__ void k_cg_update1(T *__restrict__ x, T *__restrict__ r, const T *__re
 #pragma unroll
         for (int u = 0; u < kUnroll; ++u) one(i + u * st, pv[u], xv[u], av[u], rv[u], dv[u]);
     }
-    for (; i < n; i += st) one(i, p[i], x[i], Ap[i], r[i], dinv ? dinv[i] : T(1));
-    block_sum<2>(v, sh);
+    for (; i < n; i += st) one(i, WITHX ? p[i] : T(0), WITHX ? x[i] : T(0), Ap[i], r[i], dinv ? dinv[i] : T(1));
+    block_sum<2>(v, sh + 4);  // behind the first sum's slots, which a slower wave may still read
     if (threadIdx.x == 0) {
         rz_part[2 * blockIdx.x] = v[0];
         rz_part[2 * blockIdx.x + 1] = v[1];
@@ -196,54 +205,68 @@ __global__ void k_cg_update1(T *__restrict__ x, T *__restrict__ r, const T *__re
 }
 
 // beta = rz_new / (rz_prev f) from the partial sums of (r . dinv r, r . r), formed in every
-// block; p = dinv r + beta p; Ap = 0 for the next apply (if given).  Block 0 stores
-// rz = rz_new, rr, beta and hist[2 it] = r.r, hist[2 it + 1] = breakdown flag.  f != 1 when
-// r and p were rescaled by f since rz_prev was taken (rz scales by f^2, the old direction
+// block; x += alpha p (if x is given; alpha and the freeze after a breakdown as the residual
+// update left them); p = dinv r + beta p; Ap = 0 for the next apply (if given).  Block 0 stores
+// rz = rz_new, rr, beta and hist[2 it] = r.r, hist[2 it + 1] = breakdown flag, and both in
+// host_slot (pinned host memory, if given), so that a check needs no copy of its own.  f != 1
+// when r and p were rescaled by f since rz_prev was taken (rz scales by f^2, the old direction
 // by f: one f folded into beta rescales p inside the update).
 template <class T>
-__global__ void k_cg_update2(T *__restrict__ p, const T *__restrict__ r, const T *__restrict__ dinv,
-                             T *__restrict__ Ap_zero, int64_t n, CgScalars *__restrict__ s,
-                             const double *__restrict__ rz_part, int nb, double *__restrict__ rr_hist, int it, double f)
+__global__ __launch_bounds__(256) void k_cg_update2(T *__restrict__ x, T *__restrict__ p, const T *__restrict__ r,
+                                                    const T *__restrict__ dinv, T *__restrict__ Ap_zero, int64_t n,
+                                                    CgScalars *__restrict__ s, const double *__restrict__ rz_part,
+                                                    int nb, double *__restrict__ rr_hist, int it, double f,
+                                                    double *__restrict__ host_slot)
 {
-    __shared__ double sh[2 * 256];
+    __shared__ double sh[8];
     double v[2] = {0.0, 0.0};
     for (int i = threadIdx.x; i < nb; i += 256) {
         v[0] += rz_part[2 * i];
         v[1] += rz_part[2 * i + 1];
     }
     block_sum<2>(v, sh);
-    const double rz_new = v[0], rzp = s->rz_prev;
+    const double rz_new = v[0], rzp = s->rz_prev, alpha = s->alpha;
     const double beta = (rzp != 0.0) ? rz_new / (rzp * f) : 0.0;
+    T *xw = s->frozen ? nullptr : x;  // (not written by this kernel)
     if (blockIdx.x == 0 && threadIdx.x == 0) {
         if (!isfinite(rz_new) || !isfinite(v[1])) s->breakdown = 1;
         s->beta = beta;
         s->rz = rz_new;
         s->rr = v[1];
+        const double flag = (double)s->breakdown;
         rr_hist[2 * it] = v[1];
-        rr_hist[2 * it + 1] = (double)s->breakdown;
+        rr_hist[2 * it + 1] = flag;
+        if (host_slot) {
+            host_slot[0] = v[1];
+            host_slot[1] = flag;
+        }
     }
     const int64_t st = (int64_t)gridDim.x * blockDim.x;
     int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     for (; i + (kUnroll - 1) * st < n; i += kUnroll * st) {  // loads batched
-        T rv[kUnroll], dv[kUnroll], pv[kUnroll];
+        T rv[kUnroll], dv[kUnroll], pv[kUnroll], xv[kUnroll];
 #pragma unroll
         for (int u = 0; u < kUnroll; ++u) {
             const int64_t j = i + u * st;
             rv[u] = r[j];
             dv[u] = dinv ? dinv[j] : T(1);
             pv[u] = p[j];
+            xv[u] = xw ? xw[j] : T(0);
         }
 #pragma unroll
         for (int u = 0; u < kUnroll; ++u) {
             const int64_t j = i + u * st;
             const double zi = dinv ? (double)(dv[u] * rv[u]) : (double)rv[u];
+            if (xw) xw[j] = (T)fma(alpha, (double)pv[u], (double)xv[u]);
             p[j] = (T)fma(beta, (double)pv[u], zi);
             if (Ap_zero) Ap_zero[j] = T(0);
         }
     }
     for (; i < n; i += st) {
         const double zi = dinv ? (double)(dinv[i] * r[i]) : (double)r[i];
-        p[i] = (T)fma(beta, (double)p[i], zi);
+        const T pi = p[i];
+        if (xw) xw[i] = (T)fma(alpha, (double)pi, (double)xw[i]);
+        p[i] = (T)fma(beta, (double)pi, zi);
         if (Ap_zero) Ap_zero[i] = T(0);
     }
 }
@@ -254,7 +277,7 @@ template <class T>
 __global__ void k_cg_init(const T *__restrict__ b, T *__restrict__ r, T *__restrict__ p, const T *__restrict__ dinv,
                           int64_t n, double *partial)
 {
-    __shared__ double sh[2 * 256];
+    __shared__ double sh[8];
     double v[2] = {0.0, 0.0};
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
         const T ri = b ? (T)(b[i] - r[i]) : r[i];
@@ -273,7 +296,7 @@ __global__ void k_cg_init(const T *__restrict__ b, T *__restrict__ r, T *__restr
 
 __global__ void k_cg_init_scalars(const double *partial, int nb, CgScalars *s, double *rr_hist)
 {
-    __shared__ double sh[2 * 256];
+    __shared__ double sh[8];
     double v[2] = {0.0, 0.0};
     for (int i = threadIdx.x; i < nb; i += 256) {
         v[0] += partial[2 * i];
@@ -284,6 +307,7 @@ __global__ void k_cg_init_scalars(const double *partial, int nb, CgScalars *s, d
         s->rz = v[0];
         s->rr = v[1];
         s->breakdown = 0;
+        s->frozen = 0;
         s->alpha = s->beta = s->pAp = 0.0;
         rr_hist[0] = v[1];
         rr_hist[1] = 0.0;
@@ -315,7 +339,7 @@ __global__ void k_fcg_update(double *__restrict__ x, double *__restrict__ r, dou
                              const double *__restrict__ p, const double *__restrict__ Ap, int64_t n,
                              const CgScalars *__restrict__ s, double *partial)
 {
-    __shared__ double sh[256];
+    __shared__ double sh[4];
     const double alpha = s->alpha;
     const bool frozen = s->breakdown != 0;
     double v[1] = {0.0};
@@ -334,17 +358,22 @@ __global__ void k_fcg_update(double *__restrict__ x, double *__restrict__ r, dou
     if (threadIdx.x == 0) partial[blockIdx.x] = v[0];
 }
 
-__global__ void k_fcg_rr(const double *partial, int nb, CgScalars *s, double *rr_hist, int it)
+__global__ void k_fcg_rr(const double *partial, int nb, CgScalars *s, double *rr_hist, int it, double *host_slot)
 {
-    __shared__ double sh[256];
+    __shared__ double sh[4];
     double v[1] = {0.0};
     for (int i = threadIdx.x; i < nb; i += 256) v[0] += partial[i];
     block_sum<1>(v, sh);
     if (threadIdx.x == 0) {
         if (!isfinite(v[0])) s->breakdown = 1;
         s->rr = v[0];
+        const double flag = (double)s->breakdown;
         rr_hist[2 * it] = v[0];
-        rr_hist[2 * it + 1] = (double)s->breakdown;
+        rr_hist[2 * it + 1] = flag;
+        if (host_slot) {
+            host_slot[0] = v[0];
+            host_slot[1] = flag;
+        }
     }
 }
 
@@ -352,7 +381,7 @@ __global__ void k_fcg_rr(const double *partial, int nb, CgScalars *s, double *rr
 __global__ void k_fcg_dots(const double *__restrict__ z, const double *__restrict__ r, const double *__restrict__ rold,
                            int64_t n, double *partial)
 {
-    __shared__ double sh[2 * 256];
+    __shared__ double sh[8];
     double v[2] = {0.0, 0.0};
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
         v[0] = fma(z[i], r[i], v[0]);
@@ -368,7 +397,7 @@ __global__ void k_fcg_dots(const double *__restrict__ z, const double *__restric
 // beta = (z.r - z.rold) / rz (0 for the first direction); rz = z.r
 __global__ void k_fcg_beta(const double *partial, int nb, int first, CgScalars *s)
 {
-    __shared__ double sh[2 * 256];
+    __shared__ double sh[8];
     double v[2] = {0.0, 0.0};
     for (int i = threadIdx.x; i < nb; i += 256) {
         v[0] += partial[2 * i];
@@ -446,8 +475,8 @@ hipError_t vec_axpy_f32(double *x, double a, const float *d, int64_t n, hipStrea
 template <class T>
 hipError_t vec_dot(const T *x, const T *y, int64_t n, double *partial, double *out, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_dot_partial<T>, dim3(kRedBlocks), dim3(256), 0, s, x, y, n, partial);
-    hipLaunchKernelGGL(k_reduce_to, dim3(1), dim3(256), 0, s, partial, kRedBlocks, 1, out);
+    hipLaunchKernelGGL(k_dot_partial<T>, dim3(red_blocks(n)), dim3(256), 0, s, x, y, n, partial);
+    hipLaunchKernelGGL(k_reduce_to, dim3(1), dim3(256), 0, s, partial, (int)red_blocks(n), 1, out);
     return hipGetLastError();
 }
 template hipError_t vec_dot<double>(const double *, const double *, int64_t, double *, double *, hipStream_t);
@@ -455,8 +484,8 @@ template hipError_t vec_dot<float>(const float *, const float *, int64_t, double
 
 hipError_t vec_maxabs(const double *x, int64_t n, double *partial, double *out, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_maxabs_partial, dim3(kRedBlocks), dim3(256), 0, s, x, n, partial);
-    hipLaunchKernelGGL(k_max_to, dim3(1), dim3(256), 0, s, partial, kRedBlocks, out);
+    hipLaunchKernelGGL(k_maxabs_partial, dim3(red_blocks(n)), dim3(256), 0, s, x, n, partial);
+    hipLaunchKernelGGL(k_max_to, dim3(1), dim3(256), 0, s, partial, (int)red_blocks(n), out);
     return hipGetLastError();
 }
 
@@ -464,44 +493,49 @@ template <class T>
 hipError_t cg_init(const T *b, T *r, T *p, const T *dinv, int64_t n, double *partial, CgScalars *sc, double *hist,
                    hipStream_t s)
 {
-    hipLaunchKernelGGL(k_cg_init<T>, dim3(kRedBlocks), dim3(256), 0, s, b, r, p, dinv, n, partial);
-    hipLaunchKernelGGL(k_cg_init_scalars, dim3(1), dim3(256), 0, s, partial, kRedBlocks, sc, hist);
+    hipLaunchKernelGGL(k_cg_init<T>, dim3(red_blocks(n)), dim3(256), 0, s, b, r, p, dinv, n, partial);
+    hipLaunchKernelGGL(k_cg_init_scalars, dim3(1), dim3(256), 0, s, partial, (int)red_blocks(n), sc, hist);
     return hipGetLastError();
 }
 template <class T>
 hipError_t cg_alpha(const T *p, const T *Ap, int64_t n, double *partial, CgScalars *sc, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_dot_partial<T>, dim3(kRedBlocks), dim3(256), 0, s, p, Ap, n, partial);
-    hipLaunchKernelGGL(k_cg_alpha, dim3(1), dim3(256), 0, s, partial, kRedBlocks, sc);
+    hipLaunchKernelGGL(k_dot_partial<T>, dim3(red_blocks(n)), dim3(256), 0, s, p, Ap, n, partial);
+    hipLaunchKernelGGL(k_cg_alpha, dim3(1), dim3(256), 0, s, partial, (int)red_blocks(n), sc);
     return hipGetLastError();
 }
 template <class T>
 hipError_t cg_pap(const T *p, const T *Ap, int64_t n, double *pap_part, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_dot_partial<T>, dim3(kRedBlocks), dim3(256), 0, s, p, Ap, n, pap_part);
+    hipLaunchKernelGGL(k_dot_partial<T>, dim3(red_blocks(n)), dim3(256), 0, s, p, Ap, n, pap_part);
     return hipGetLastError();
 }
 template <class T>
-hipError_t cg_update_xr(T *x, T *r, const T *p, const T *Ap, const T *dinv, int64_t n, const double *pap_part,
-                        double *rz_part, CgScalars *sc, hipStream_t s)
+hipError_t cg_update_xr(T *x, T *r, const T *p, const T *Ap, const T *dinv, bool masked, int64_t n,
+                        const double *pap_part, double *rz_part, CgScalars *sc, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_cg_update1<T>, dim3(kRedBlocks), dim3(256), 0, s, x, r, p, Ap, dinv, n, sc, pap_part,
-                       kRedBlocks, rz_part);
+    const unsigned nb = red_blocks(n);
+    auto launch = [&](auto kern) {
+        hipLaunchKernelGGL(kern, dim3(nb), dim3(256), 0, s, x, r, p, Ap, dinv, n, sc, pap_part, (int)nb, rz_part);
+    };
+    if (x) masked ? launch(k_cg_update1<T, true, true>) : launch(k_cg_update1<T, true, false>);
+    else masked ? launch(k_cg_update1<T, false, true>) : launch(k_cg_update1<T, false, false>);
     return hipGetLastError();
 }
 template <class T>
 hipError_t cg_rz_partials(const T *r, const T *dinv, int64_t n, double *rz_part, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_cg_init<T>, dim3(kRedBlocks), dim3(256), 0, s, nullptr, const_cast<T *>(r), nullptr, dinv, n,
+    hipLaunchKernelGGL(k_cg_init<T>, dim3(red_blocks(n)), dim3(256), 0, s, nullptr, const_cast<T *>(r), nullptr, dinv, n,
                        rz_part);
     return hipGetLastError();
 }
 template <class T>
-hipError_t cg_update_dir(T *p, const T *r, const T *dinv, T *Ap_zero, int64_t n, const double *rz_part, CgScalars *sc,
-                         double *hist, int it, double f, hipStream_t s)
+hipError_t cg_update_dir(T *x, T *p, const T *r, const T *dinv, T *Ap_zero, int64_t n, const double *rz_part,
+                         CgScalars *sc, double *hist, int it, double f, double *host_slot, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_cg_update2<T>, dim3(kRedBlocks), dim3(256), 0, s, p, r, dinv, Ap_zero, n, sc, rz_part,
-                       kRedBlocks, hist, it, f);
+    const unsigned nb = red_blocks(n);
+    hipLaunchKernelGGL(k_cg_update2<T>, dim3(nb), dim3(256), 0, s, x, p, r, dinv, Ap_zero, n, sc, rz_part, (int)nb,
+                       hist, it, f, host_slot);
     return hipGetLastError();
 }
 #define HEXPA_INST(T)                                                                                           \
@@ -509,19 +543,19 @@ hipError_t cg_update_dir(T *p, const T *r, const T *dinv, T *Ap_zero, int64_t n,
                                    hipStream_t);                                                               \
     template hipError_t cg_alpha<T>(const T *, const T *, int64_t, double *, CgScalars *, hipStream_t);         \
     template hipError_t cg_pap<T>(const T *, const T *, int64_t, double *, hipStream_t);                      \
-    template hipError_t cg_update_xr<T>(T *, T *, const T *, const T *, const T *, int64_t, const double *,    \
-                                        double *, CgScalars *, hipStream_t);                                   \
+    template hipError_t cg_update_xr<T>(T *, T *, const T *, const T *, const T *, bool, int64_t,              \
+                                        const double *, double *, CgScalars *, hipStream_t);                   \
     template hipError_t cg_rz_partials<T>(const T *, const T *, int64_t, double *, hipStream_t);              \
-    template hipError_t cg_update_dir<T>(T *, const T *, const T *, T *, int64_t, const double *, CgScalars *, \
-                                         double *, int, double, hipStream_t);
+    template hipError_t cg_update_dir<T>(T *, T *, const T *, const T *, T *, int64_t, const double *,         \
+                                         CgScalars *, double *, int, double, double *, hipStream_t);
 HEXPA_INST(double)
 HEXPA_INST(float)
 
 hipError_t fcg_update(double *x, double *r, double *rold, const double *p, const double *Ap, int64_t n,
-                      double *partial, CgScalars *sc, double *hist, int it, hipStream_t s)
+                      double *partial, CgScalars *sc, double *hist, int it, double *host_slot, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_fcg_update, dim3(kRedBlocks), dim3(256), 0, s, x, r, rold, p, Ap, n, sc, partial);
-    hipLaunchKernelGGL(k_fcg_rr, dim3(1), dim3(256), 0, s, partial, kRedBlocks, sc, hist, it);
+    hipLaunchKernelGGL(k_fcg_update, dim3(red_blocks(n)), dim3(256), 0, s, x, r, rold, p, Ap, n, sc, partial);
+    hipLaunchKernelGGL(k_fcg_rr, dim3(1), dim3(256), 0, s, partial, (int)red_blocks(n), sc, hist, it, host_slot);
     return hipGetLastError();
 }
 
@@ -529,9 +563,9 @@ hipError_t fcg_direction(const double *z, const double *r, const double *rold, d
                          CgScalars *sc, hipStream_t s)
 {
     const int first = rold ? 0 : 1;
-    hipLaunchKernelGGL(k_fcg_dots, dim3(kRedBlocks), dim3(256), 0, s, z, r, rold, n, partial);
-    hipLaunchKernelGGL(k_fcg_beta, dim3(1), dim3(256), 0, s, partial, kRedBlocks, first, sc);
-    hipLaunchKernelGGL(k_fcg_p, dim3(kRedBlocks), dim3(256), 0, s, p, z, n, first, sc);
+    hipLaunchKernelGGL(k_fcg_dots, dim3(red_blocks(n)), dim3(256), 0, s, z, r, rold, n, partial);
+    hipLaunchKernelGGL(k_fcg_beta, dim3(1), dim3(256), 0, s, partial, (int)red_blocks(n), first, sc);
+    hipLaunchKernelGGL(k_fcg_p, dim3(red_blocks(n)), dim3(256), 0, s, p, z, n, first, sc);
     return hipGetLastError();
 }
 
