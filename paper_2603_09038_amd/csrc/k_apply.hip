@@ -12,6 +12,7 @@
 
 #include "apply_passes.h"
 #include "apply_chain.h"
+#include "apply_pencil.h"
 #include "geometry.h"
 
 namespace hexpa {
@@ -455,7 +456,8 @@ __global__ __launch_bounds__(256) void k_dstep(int64_t npts, const T *__restrict
 // So the D stream of the next group overlaps the transposed passes and the forward
 // passes, and the gathers overlap the forward passes, without holding registers.
 // (FP64 with MFMA contractions runs the chained kernel at these orders; this one serves the
-// vector-ALU and the 16-bit executors, and the mass operator at p = 4.)
+// vector-ALU and the 16-bit executors, and the mass operator at p = 4 but with the vector ALU,
+// which has the pencil kernel there.)
 constexpr int kDmaMinD = 6;                // orders p >= 5 (measured faster there; diffusion at p <= 4 keeps the register kernel)
 constexpr int kDmaLdsBudget = 53 * 1024;   // LDS bytes per workgroup of the DMA kernel
 
@@ -804,6 +806,14 @@ static hipError_t launch_k(const pa_op *op, const typename ExT<EX>::T *qd, const
         hipLaunchKernelGGL(kern, dim3(std::min(cap, (n + run - 1) / run)), dim3(NT), 0, s, n, run, elist,
                            op->d_elem_dofs, qd, op->d_tab, x, y);
         return hipGetLastError();
+    } else if constexpr (EX == EX_VALU64 && ATOMIC && PencilShape<D, Q, OPS>::ok) {  // FP64 vector ALU, z in registers
+        using S = PencilShape<D, Q, OPS>;
+        const int ngroups = (n + S::E - 1) / S::E;
+        if (ngroups == 0) return hipSuccess;
+        constexpr auto kern = k_apply_pencil<D, Q, OPS>;
+        hipLaunchKernelGGL(kern, dim3(capped(op, persistent_blocks<kern>(S::NT, ngroups))), dim3(S::NT), 0, s, n,
+                           ngroups, op->d_elem_dofs, qd, op->d_tab, x, y);
+        return hipGetLastError();
     } else {
         return launch_groups<D, Q, OPS, EX, ATOMIC>(op, qd, x, y, elist, n, s);
     }
@@ -885,6 +895,11 @@ static void group_shape(int *elems, int *threads)
     if constexpr (FUSED_STORED && EX == EX_MFMA64 && ChainShape<D, Q, OPS>::ok) {
         *elems = 1;
         *threads = ChainShape<D, Q, OPS>::NT;
+        return;
+    }
+    if constexpr (FUSED_STORED && EX == EX_VALU64 && PencilShape<D, Q, OPS>::ok) {
+        *elems = PencilShape<D, Q, OPS>::E;
+        *threads = PencilShape<D, Q, OPS>::NT;
         return;
     }
     constexpr bool DMA = FUSED_STORED && DmaShape<D, Q, OPS, T>::ok;
