@@ -121,6 +121,7 @@ extern "C" void pa_destroy(pa_op *op)
     dfree(op->d_tab);
     dfree(op->d_grid);
     dfree(op->d_ess);
+    dfree(op->d_ess_bits);
     dfree(op->d_color_elems);
     dfree(op->d_scratch);
     delete op;
@@ -251,6 +252,10 @@ extern "C" int pa_setup(const pa_mesh_desc *m, int order, int q1d, const pa_coef
     if (!ess.empty()) {
         HIP_OK(dalloc(&op->d_ess, ess.size()));
         HIP_OK(hipMemcpy(op->d_ess, ess.data(), ess.size() * sizeof(int32_t), hipMemcpyHostToDevice));
+        std::vector<uint32_t> bits(((size_t)op->ndof + 31) / 32, 0u);
+        for (const int32_t e : ess) bits[e >> 5] |= 1u << (e & 31);
+        HIP_OK(dalloc(&op->d_ess_bits, bits.size()));
+        HIP_OK(hipMemcpy(op->d_ess_bits, bits.data(), bits.size() * sizeof(uint32_t), hipMemcpyHostToDevice));
     }
     if (!colors.empty()) {
         HIP_OK(dalloc(&op->d_color_elems, colors.size()));
@@ -333,9 +338,8 @@ extern "C" int pa_apply_add(pa_op *op, const double *x, double *y, void *stream)
 int hexpa::do_apply_constrained(pa_op *op, const double *x, double *y, hipStream_t s)
 {
     if (op->ness == 0) return do_apply(op, op->variant, x, y, s);
-    HIP_OK(vec_copy(op->d_scratch, x, op->ndof, s));
-    HIP_OK(vec_zero_list(op->d_scratch, op->d_ess, op->ness, s));
-    int rc = do_apply(op, op->variant, op->d_scratch, y, s);
+    HIP_OK(vec_mask_start(op->d_scratch, y, x, op->d_ess_bits, op->ndof, s));
+    int rc = do_apply(op, op->variant, op->d_scratch, y, s, false);
     if (rc) return rc;
     HIP_OK(vec_copy_list(y, x, op->d_ess, op->ness, s));
     return PA_OK;

@@ -64,6 +64,7 @@ struct pa_op {
     double *d_grid = nullptr;        // coefficient grid (device copy)
     hexpa::CoeffDev coeff{};         // coefficient as the kernels see it (grid -> d_grid)
     int32_t *d_ess = nullptr;        // [ness]
+    uint32_t *d_ess_bits = nullptr;  // [(ndof + 31) / 32]: bit i & 31 of word i >> 5 is set on essential DOFs
     // colour classes: elements of colour c are d_color_elems[color_off[c] .. color_off[c+1])
     int32_t *d_color_elems = nullptr;
     int color_off[9] = {0};
@@ -100,6 +101,8 @@ pa_op *lp_operator(const pa_lp *lp);
 // vector kernels (k_vec.hip)
 hipError_t vec_fill(double *y, double v, int64_t n, hipStream_t s);
 hipError_t vec_copy(double *y, const double *x, int64_t n, hipStream_t s);
+// m = x with the marked entries zero, y = 0
+hipError_t vec_mask_start(double *m, double *y, const double *x, const uint32_t *bits, int64_t n, hipStream_t s);
 hipError_t vec_zero_list(double *y, const int32_t *list, int n, hipStream_t s);
 hipError_t vec_copy_list(double *y, const double *x, const int32_t *list, int n, hipStream_t s);
 hipError_t vec_set_list(double *y, double v, const int32_t *list, int n, hipStream_t s);

@@ -30,6 +30,17 @@ __global__ void k_copy(double *y, const double *x, int64_t n)
 {
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) y[i] = x[i];
 }
+// The start of a constrained apply in one pass: the masked input and the cleared result.
+// Bound by memory (24 B a DOF and one bit).  33^3 elements, p = 3: 6.2 us where a copy, a
+// clear of the list and a fill took 12.0 in three launches.
+__global__ void k_mask_start(double *__restrict__ m, double *__restrict__ y, const double *__restrict__ x,
+                             const uint32_t *__restrict__ bits, int64_t n)
+{
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
+        m[i] = (bits[i >> 5] >> (i & 31)) & 1u ? 0.0 : x[i];
+        y[i] = 0.0;
+    }
+}
 template <class T>
 __global__ void k_set_list(T *y, T v, const int32_t *list, int n)
 {
@@ -436,6 +447,12 @@ hipError_t vec_copy(double *y, const double *x, int64_t n, hipStream_t s)
 {
     if (n <= 0) return hipSuccess;
     hipLaunchKernelGGL(k_copy, dim3(min(nblk(n), 8192u)), dim3(256), 0, s, y, x, n);
+    return hipGetLastError();
+}
+hipError_t vec_mask_start(double *m, double *y, const double *x, const uint32_t *bits, int64_t n, hipStream_t s)
+{
+    if (n <= 0) return hipSuccess;
+    hipLaunchKernelGGL(k_mask_start, dim3(min(nblk(n), 8192u)), dim3(256), 0, s, m, y, x, bits, n);
     return hipGetLastError();
 }
 hipError_t vec_set_list(double *y, double v, const int32_t *list, int n, hipStream_t s)
