@@ -68,27 +68,23 @@ __global__ void k_loss_scale(double *g, int64_t n, double *sc)
 }
 
 // ---------------------------------------------------------------- coarse level
-// 1-D weight of coarse vertex a at fine lattice index I: the fine node lies in element
-// ex = min(I / p, n - 1) at GLL coordinate xi = gll[I - ex p]; the p=1 basis there is
-// (1 - xi) at vertex ex and xi at vertex ex + 1.
-__device__ inline double w1d(int64_t I, int64_t a, int n, int p, const double *gll)
-{
-    const int64_t ex = min(I / p, (int64_t)n - 1);
-    const double xi = gll[I - ex * p];
-    return a == ex ? 1.0 - xi : (a == ex + 1 ? xi : 0.0);
-}
-
+// uf = P1 u1, plus uf or m1 * m2 where given.  Bound by memory; 32-bit indexes (a lattice has
+// fewer than 2^31 points) since 64-bit divisions by run-time sizes cost more than the traffic:
+// 129^3 points, with the product 18.4 us; the product 9.4 and the sum 16.9 before.
+enum { PROLONG_SET, PROLONG_ADD, PROLONG_MUL };
 __global__ void k_prolong(BoxDims b, const double *__restrict__ gll, const double *__restrict__ u1,
-                          double *__restrict__ uf, int add)
+                          double *__restrict__ uf, int mode, const double *__restrict__ m1,
+                          const double *__restrict__ m2)
 {
-    const int64_t Mx = (int64_t)b.nx * b.p + 1, My = (int64_t)b.ny * b.p + 1, Mz = (int64_t)b.nz * b.p + 1;
-    const int64_t Cx = b.nx + 1, Cy = b.ny + 1;
-    const int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const uint32_t p = b.p, Mx = b.nx * p + 1, My = b.ny * p + 1, Mz = b.nz * p + 1;
+    const uint32_t Cx = b.nx + 1, Cy = b.ny + 1;
+    const uint32_t g = blockIdx.x * blockDim.x + threadIdx.x;
     if (g >= Mx * My * Mz) return;
-    const int64_t I = g % Mx, J = (g / Mx) % My, K = g / (Mx * My);
-    const int64_t ex = min(I / b.p, (int64_t)b.nx - 1), ey = min(J / b.p, (int64_t)b.ny - 1),
-                  ez = min(K / b.p, (int64_t)b.nz - 1);
-    const double x = gll[I - ex * b.p], y = gll[J - ey * b.p], z = gll[K - ez * b.p];
+    const double base = mode == PROLONG_ADD ? uf[g] : mode == PROLONG_MUL ? m1[g] * m2[g] : 0.0;
+    const uint32_t K = g / (Mx * My), R = g - K * (Mx * My), J = R / Mx, I = R - J * Mx;
+    const uint32_t ex = min(I / p, (uint32_t)b.nx - 1), ey = min(J / p, (uint32_t)b.ny - 1),
+                   ez = min(K / p, (uint32_t)b.nz - 1);
+    const double x = gll[I - ex * p], y = gll[J - ey * p], z = gll[K - ez * p];
     double v = 0.0;
 #pragma unroll
     for (int c = 0; c < 8; ++c) {
@@ -96,7 +92,7 @@ __global__ void k_prolong(BoxDims b, const double *__restrict__ gll, const doubl
         const double w = (ca ? x : 1.0 - x) * (cb ? y : 1.0 - y) * (cc ? z : 1.0 - z);
         v += w * u1[(ex + ca) + Cx * ((ey + cb) + Cy * (ez + cc))];
     }
-    uf[g] = add ? uf[g] + v : v;
+    uf[g] = mode == PROLONG_SET ? v : base + v;
 }
 
 // Restriction r1 = P1^T rf, separable: the weight of fine node (I,J,K) at coarse vertex
@@ -104,23 +100,28 @@ __global__ void k_prolong(BoxDims b, const double *__restrict__ gll, const doubl
 // the at most 2p + 1 fine lattice points whose 1-D weight for a coarse index is nonzero,
 // in a fixed order (no atomics).  Pass `axis` maps in[nz'][ny'][nx'] to out with that
 // axis shortened from M = n p + 1 to n + 1.
-__global__ void k_restrict_axis(int axis, int n, int p, int64_t nx_in, int64_t ny_in, int64_t nz_in,
+// The 1-D weight: a fine node in element ex at GLL coordinate xi weighs 1 - xi at vertex ex and
+// xi at ex + 1.  All loads of a point are in flight together.  129^3 to
+// 33^3 points: 8.3 -> 7.4 us an axis.
+__global__ void k_restrict_axis(int axis, uint32_t n, uint32_t p, uint32_t nx_in, uint32_t ny_in, uint32_t nz_in,
                                 const double *__restrict__ gll, const double *__restrict__ in,
                                 double *__restrict__ out)
 {
-    const int64_t C = n + 1, M = (int64_t)n * p + 1;
-    const int64_t ox = axis == 0 ? C : nx_in, oy = axis == 1 ? C : ny_in, oz = axis == 2 ? C : nz_in;
-    const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const uint32_t C = n + 1, M = n * p + 1;
+    const uint32_t ox = axis == 0 ? C : nx_in, oy = axis == 1 ? C : ny_in, oz = axis == 2 ? C : nz_in;
+    const uint32_t idx = blockIdx.x * blockDim.x + threadIdx.x;
     if (idx >= ox * oy * oz) return;
-    const int64_t i = idx % ox, j = (idx / ox) % oy, k = idx / (ox * oy);
-    const int64_t a = axis == 0 ? i : (axis == 1 ? j : k);  // coarse index along the axis
-    const int64_t stride = axis == 0 ? 1 : (axis == 1 ? nx_in : nx_in * ny_in);
-    const int64_t base = (axis == 0 ? 0 : i) + nx_in * ((axis == 1 ? 0 : j) + ny_in * (axis == 2 ? 0 : k));
-    const int64_t I0 = max((int64_t)0, (a - 1) * p), I1 = min(M - 1, (a + 1) * p);
+    const uint32_t k = idx / (ox * oy), rem = idx - k * (ox * oy), j = rem / ox, i = rem - j * ox;
+    const uint32_t a = axis == 0 ? i : (axis == 1 ? j : k);  // coarse index along the axis
+    const uint32_t stride = axis == 0 ? 1 : (axis == 1 ? nx_in : nx_in * ny_in);
+    const uint32_t base = (axis == 0 ? 0 : i) + nx_in * ((axis == 1 ? 0 : j) + ny_in * (axis == 2 ? 0 : k));
+    const uint32_t I0 = a > 0 ? (a - 1) * p : 0, I1 = min(M - 1, (a + 1) * p);
     double acc = 0.0;
-    for (int64_t I = I0; I <= I1; ++I) {
-        const double w = w1d(I, a, n, p, gll);
-        if (w != 0.0) acc = fma(w, in[base + I * stride], acc);
+#pragma unroll 4
+    for (uint32_t I = I0; I <= I1; ++I) {  // the weight of vertex a at I; the last node has no element to its right
+        const double w = I < a * p ? gll[I - (a - 1) * p] : a < n ? 1.0 - gll[I - a * p] : gll[p];
+        const double v = in[base + I * stride];
+        acc = w != 0.0 ? fma(w, v, acc) : acc;
     }
     out[idx] = acc;
 }
@@ -167,120 +168,108 @@ __global__ void k_dinv_center(int64_t n1, const double *__restrict__ S, double *
     if (i < n1) dinv[i] = 1.0 / S[13 * n1 + i];
 }
 
-// Block sum in a fixed order; the last workgroup to finish adds the per-block partials in
-// block order and hands the total to fin (thread 0 only), then re-arms the counter.
-// Blocks of kCoarseThreads threads (small blocks spread the 27-point stencil over more CUs).
-constexpr int kCoarseThreads = 256;
-template <class F>
-__device__ inline void grid_sum_last(double v, double *partial, unsigned int *count, F fin)
+// Coarse PCG.  Every kernel leaves one partial sum per block, and each block of the next one
+// adds them all in the same fixed order: no counter, no last block and, above all, no device
+// fence, which writes the L2 of every XCD back.  The grid is capped so that this stays a few
+// loads a thread.  33^3 unknowns: init / a / b 7.4 / 15.2 / 8.0 ->
+// 4.8 / 8.7 / 4.8 us.  What is left of them is launch, one pass of latency and the sums.
+constexpr int kCoarseThreads = 256, kCoarseBlocks = kCoarsePartials / 2;
+// block-wide sum in a fixed order (a shuffle tree in each wave, then the wave sums); every
+// thread gets it.  sh: 4 doubles, not used again before a barrier.
+__device__ inline double coarse_sum(double v, double *sh)
 {
-    __shared__ double sh[kCoarseThreads];
-    __shared__ int last;
     const int t = threadIdx.x;
-    sh[t] = v;
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
+    if ((t & 63) == 0) sh[t >> 6] = v;
     __syncthreads();
-    for (int h = kCoarseThreads / 2; h > 0; h >>= 1) {
-        if (t < h) sh[t] += sh[t + h];
-        __syncthreads();
-    }
-    if (t == 0) {
-        partial[blockIdx.x] = sh[0];
-        __threadfence();
-        const unsigned prev = atomicAdd(count, 1u);
-        last = prev == gridDim.x - 1;
-    }
-    __syncthreads();
-    if (!last) return;
-    __threadfence();
-    double a = 0.0;
-    for (int i = t; i < (int)gridDim.x; i += kCoarseThreads)
-        a += __hip_atomic_load(partial + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    sh[t] = a;
-    __syncthreads();
-    for (int h = kCoarseThreads / 2; h > 0; h >>= 1) {
-        if (t < h) sh[t] += sh[t + h];
-        __syncthreads();
-    }
-    if (t == 0) {
-        fin(sh[0]);
-        __hip_atomic_store(count, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
+    return (sh[0] + sh[1]) + (sh[2] + sh[3]);
+}
+__device__ inline double coarse_total(const double *__restrict__ partial, double *sh)
+{
+    double v = 0.0;
+    for (int i = threadIdx.x; i < (int)gridDim.x; i += kCoarseThreads) v += partial[i];
+    return coarse_sum(v, sh);
 }
 
-// u = 0, z = dinv r, p0 = 0; rz = r.z, beta = 0
+// u = 0, z = dinv r, p0 = 0; partial sums of r.z
 __global__ __launch_bounds__(kCoarseThreads) void k_cpcg_init(int64_t n1, const double *__restrict__ dinv,
                                                    const double *__restrict__ r, double *__restrict__ u,
-                                                   double *__restrict__ z, double *__restrict__ p0, double *partial,
-                                                   CoarseScalars *sc)
+                                                   double *__restrict__ z, double *__restrict__ p0,
+                                                   double *__restrict__ prz)
 {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    __shared__ double sh[4];
     double v = 0.0;
-    if (i < n1) {
+    for (int64_t i = (int64_t)blockIdx.x * kCoarseThreads + threadIdx.x; i < n1; i += (int64_t)gridDim.x * kCoarseThreads) {
         const double zi = dinv[i] * r[i];
         z[i] = zi;
         u[i] = 0.0;
         p0[i] = 0.0;
-        v = r[i] * zi;
+        v = fma(r[i], zi, v);
     }
-    grid_sum_last(v, partial, &sc->count, [&](double tot) {
-        sc->rz = tot;
-        sc->beta = 0.0;
-    });
+    v = coarse_sum(v, sh);
+    if (threadIdx.x == 0) prz[blockIdx.x] = v;
 }
 
-// p1 = z + beta p0; Ap = S (z + beta p0); alpha = rz / (p1 . Ap)
-__global__ __launch_bounds__(kCoarseThreads) void k_cpcg_a(BoxDims b, const double *__restrict__ S,
+// beta = r.z / (the r.z before it), 0 in iteration 0; p1 = z + beta p0; Ap = S (z + beta p0);
+// partial sums of p1 . Ap.  A neighbour outside the box is read as the point itself and counted
+// as zero, so that all loads of a point are in flight together.
+__global__ __launch_bounds__(kCoarseThreads) void k_cpcg_a(BoxDims b, int it, const double *__restrict__ S,
                                                 const double *__restrict__ z, const double *__restrict__ p0,
-                                                double *__restrict__ p1, double *__restrict__ Ap, double *partial,
+                                                double *__restrict__ p1, double *__restrict__ Ap,
+                                                const double *__restrict__ prz, double *__restrict__ ppAp,
                                                 CoarseScalars *sc)
 {
-    const int64_t Cx = b.nx + 1, Cy = b.ny + 1, Cz = b.nz + 1, n1 = Cx * Cy * Cz;
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const double beta = sc->beta;
+    __shared__ double sh[4], sh2[4];
+    const int Cx = b.nx + 1, Cy = b.ny + 1, Cz = b.nz + 1;
+    const int64_t n1 = (int64_t)Cx * Cy * Cz;
+    const double rz = coarse_total(prz, sh), old = it > 0 ? sc->rz[(it - 1) & 1] : 0.0;
+    const double beta = old > 0.0 ? rz / old : 0.0;
+    if (blockIdx.x == 0 && threadIdx.x == 0) sc->rz[it & 1] = rz;
     double v = 0.0;
-    if (i < n1) {
-        const int64_t I = i % Cx, J = (i / Cx) % Cy, K = i / (Cx * Cy);
+    for (int64_t i = (int64_t)blockIdx.x * kCoarseThreads + threadIdx.x; i < n1; i += (int64_t)gridDim.x * kCoarseThreads) {
+        const uint32_t i32 = (uint32_t)i, K = i32 / (uint32_t)(Cx * Cy), R = i32 - K * (uint32_t)(Cx * Cy);
+        const int J = R / (uint32_t)Cx, I = R - J * (uint32_t)Cx;
         double acc = 0.0;
 #pragma unroll
         for (int s = 0; s < 27; ++s) {
             const int dx = s % 3 - 1, dy = (s / 3) % 3 - 1, dz = s / 9 - 1;
-            const int64_t In = I + dx, Jn = J + dy, Kn = K + dz;
-            if (In < 0 || In >= Cx || Jn < 0 || Jn >= Cy || Kn < 0 || Kn >= Cz) continue;
-            const int64_t j = i + dx + Cx * (dy + Cy * dz);
-            acc = fma(S[s * n1 + i], z[j] + beta * p0[j], acc);
+            const bool in = (unsigned)(I + dx) < (unsigned)Cx && (unsigned)(J + dy) < (unsigned)Cy &&
+                            (unsigned)((int)K + dz) < (unsigned)Cz;
+            const int64_t j = in ? i + dx + (int64_t)Cx * (dy + Cy * dz) : i;
+            const double w = z[j] + beta * p0[j];
+            acc = fma(S[s * n1 + i], in ? w : 0.0, acc);
         }
         const double pi = z[i] + beta * p0[i];
         p1[i] = pi;
         Ap[i] = acc;
-        v = pi * acc;
+        v = fma(pi, acc, v);
     }
-    grid_sum_last(v, partial, &sc->count, [&](double tot) {
-        sc->pAp = tot;
-        sc->alpha = tot > 0.0 ? sc->rz / tot : 0.0;
-    });
+    v = coarse_sum(v, sh2);
+    if (threadIdx.x == 0) ppAp[blockIdx.x] = v;
 }
 
-// u += alpha p1; r -= alpha Ap; z = dinv r; beta = (r.z)_new / rz
-__global__ __launch_bounds__(kCoarseThreads) void k_cpcg_b(int64_t n1, const double *__restrict__ dinv,
+// alpha = rz / (p1 . Ap); u += alpha p1; r -= alpha Ap; z = dinv r; partial sums of r.z
+__global__ __launch_bounds__(kCoarseThreads) void k_cpcg_b(int64_t n1, int it, const double *__restrict__ dinv,
                                                 const double *__restrict__ p1, const double *__restrict__ Ap,
                                                 double *__restrict__ u, double *__restrict__ r,
-                                                double *__restrict__ z, double *partial, CoarseScalars *sc)
+                                                double *__restrict__ z, const double *__restrict__ ppAp,
+                                                double *__restrict__ prz, const CoarseScalars *__restrict__ sc)
 {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const double alpha = sc->alpha;
+    __shared__ double sh[4], sh2[4];
+    const double pAp = coarse_total(ppAp, sh);
+    const double alpha = pAp > 0.0 ? sc->rz[it & 1] / pAp : 0.0;
     double v = 0.0;
-    if (i < n1) {
+    for (int64_t i = (int64_t)blockIdx.x * kCoarseThreads + threadIdx.x; i < n1; i += (int64_t)gridDim.x * kCoarseThreads) {
         u[i] = fma(alpha, p1[i], u[i]);
         const double ri = fma(-alpha, Ap[i], r[i]);
         r[i] = ri;
         const double zi = dinv[i] * ri;
         z[i] = zi;
-        v = ri * zi;
+        v = fma(ri, zi, v);
     }
-    grid_sum_last(v, partial, &sc->count, [&](double tot) {
-        sc->beta = sc->rz > 0.0 ? tot / sc->rz : 0.0;
-        sc->rz = tot;
-    });
+    v = coarse_sum(v, sh2);
+    if (threadIdx.x == 0) prz[blockIdx.x] = v;
 }
 
 // ---------------------------------------------------------------- FP16 MFMA inference
@@ -593,10 +582,12 @@ hipError_t vec_loss_scale(double *g, int64_t n, double *sc, hipStream_t s)
     return hipGetLastError();
 }
 
-hipError_t coarse_prolong(const BoxDims &b, const double *gll, const double *u1, double *uf, bool add, hipStream_t s)
+hipError_t coarse_prolong(const BoxDims &b, const double *gll, const double *u1, double *uf, bool add,
+                          const double *m1, const double *m2, hipStream_t s)
 {
     const int64_t nf = ((int64_t)b.nx * b.p + 1) * ((int64_t)b.ny * b.p + 1) * ((int64_t)b.nz * b.p + 1);
-    hipLaunchKernelGGL(k_prolong, dim3(nblk(nf)), dim3(256), 0, s, b, gll, u1, uf, add ? 1 : 0);
+    const int mode = m1 ? PROLONG_MUL : add ? PROLONG_ADD : PROLONG_SET;
+    hipLaunchKernelGGL(k_prolong, dim3(nblk(nf)), dim3(256), 0, s, b, gll, u1, uf, mode, m1, m2);
     return hipGetLastError();
 }
 
@@ -637,12 +628,13 @@ hipError_t coarse_pcg(const BoxDims &b, const double *S, const double *dinv, dou
                       hipStream_t s)
 {
     const int64_t n1 = (int64_t)(b.nx + 1) * (b.ny + 1) * (b.nz + 1);
-    const unsigned nb = (unsigned)((n1 + kCoarseThreads - 1) / kCoarseThreads);
-    hipLaunchKernelGGL(k_cpcg_init, dim3(nb), dim3(kCoarseThreads), 0, s, n1, dinv, r1, u, z, p0, partial, sc);
+    const unsigned nb = (unsigned)std::min<int64_t>((n1 + kCoarseThreads - 1) / kCoarseThreads, kCoarseBlocks);
+    double *prz = partial, *ppAp = partial + kCoarseBlocks;
+    hipLaunchKernelGGL(k_cpcg_init, dim3(nb), dim3(kCoarseThreads), 0, s, n1, dinv, r1, u, z, p0, prz);
     for (int k = 0; k < iters; ++k) {
         double *pin = (k & 1) ? p1 : p0, *pout = (k & 1) ? p0 : p1;
-        hipLaunchKernelGGL(k_cpcg_a, dim3(nb), dim3(kCoarseThreads), 0, s, b, S, z, pin, pout, Ap, partial, sc);
-        hipLaunchKernelGGL(k_cpcg_b, dim3(nb), dim3(kCoarseThreads), 0, s, n1, dinv, pout, Ap, u, r1, z, partial, sc);
+        hipLaunchKernelGGL(k_cpcg_a, dim3(nb), dim3(kCoarseThreads), 0, s, b, k, S, z, pin, pout, Ap, prz, ppAp, sc);
+        hipLaunchKernelGGL(k_cpcg_b, dim3(nb), dim3(kCoarseThreads), 0, s, n1, k, dinv, pout, Ap, u, r1, z, ppAp, prz, sc);
     }
     return hipGetLastError();
 }

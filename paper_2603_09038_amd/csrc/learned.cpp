@@ -228,7 +228,7 @@ int bind(pa_lp *lp, pa_op *op, hipStream_t s)
     HIP_OK(dalloc(&lp->cp0, n1));
     HIP_OK(dalloc(&lp->cp1, n1));
     HIP_OK(dalloc(&lp->cAp, n1));
-    HIP_OK(dalloc(&lp->cpart, (n1 + 255) / 256));  // one partial per coarse block (256 threads)
+    HIP_OK(dalloc(&lp->cpart, kCoarsePartials));
     HIP_OK(dalloc(&lp->csc, 1));
     {
         const int64_t My = (int64_t)op->ny * op->p + 1, Mz = (int64_t)op->nz * op->p + 1;
@@ -299,16 +299,17 @@ int ensure_coarse_graph(pa_lp *lp)
     return PA_OK;
 }
 
-// z (+)= P1 A1^{-1} P1^T r
-int coarse_part(pa_lp *lp, const double *r, double *z, bool add, hipStream_t s)
+// z (+)= P1 A1^{-1} P1^T r, then zero on the essential DOFs; with m, z = m * r + P1 A1^{-1} P1^T r
+// and the essential DOFs are left to the caller
+int coarse_part(pa_lp *lp, const double *r, double *z, bool add, hipStream_t s, const double *m = nullptr)
 {
     HIP_OK(coarse_restrict(lp->box, lp->gll, r, lp->cr, lp->ct1, lp->ct2, s));
     if (lp->ncess) HIP_OK(vec_zero_list(lp->cr, lp->cess, lp->ncess, s));
     int rc = ensure_coarse_graph(lp);
     if (rc) return rc;
     HIP_OK(hipGraphLaunch(lp->cexec, s));
-    HIP_OK(coarse_prolong(lp->box, lp->gll, lp->cu, z, add, s));
-    if (lp->op->ness) HIP_OK(vec_zero_list(z, lp->op->d_ess, lp->op->ness, s));
+    HIP_OK(coarse_prolong(lp->box, lp->gll, lp->cu, z, add, m, r, s));
+    if (!m && lp->op->ness) HIP_OK(vec_zero_list(z, lp->op->d_ess, lp->op->ness, s));
     return PA_OK;
 }
 
@@ -432,18 +433,16 @@ extern "C" int pa_lp_logk(pa_lp *lp, float *dev_out)
 
 int hexpa::lp_precondition(pa_lp *lp, const double *r, double *z, hipStream_t s)
 {
-    // Jacobi, plus the network's learned correction
-    HIP_OK(vec_mul(z, lp->dinv, r, lp->ndof, s));
-    if (lp->o.use_net) {
-        int rc = net_part(lp, r, z, s, lp->o.infer_fp16 != 0, true, lp->o.net_scale > 0.0 ? lp->o.net_scale : 1.0);
-        if (rc) return rc;
-    }
+    // Jacobi, plus the coarse correction (one pass over z), plus the network's learned one
     if (lp->o.use_coarse) {
-        int rc = coarse_part(lp, r, z, true, s);
+        int rc = coarse_part(lp, r, z, false, s, lp->dinv);
         if (rc) return rc;
-    } else if (lp->op->ness) {
-        HIP_OK(vec_zero_list(z, lp->op->d_ess, lp->op->ness, s));
+    } else {
+        HIP_OK(vec_mul(z, lp->dinv, r, lp->ndof, s));
     }
+    if (lp->o.use_net)  // clears the essential DOFs
+        return net_part(lp, r, z, s, lp->o.infer_fp16 != 0, true, lp->o.net_scale > 0.0 ? lp->o.net_scale : 1.0);
+    if (lp->op->ness) HIP_OK(vec_zero_list(z, lp->op->d_ess, lp->op->ness, s));
     return PA_OK;
 }
 
