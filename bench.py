@@ -37,11 +37,11 @@ HBM_PEAK_GBS = 8000.0     # MI355X HBM3E
 FP64_PEAK_TFLOPS = 78.6   # MI355X dense FP64 (vector and MFMA alike)
 METRIC = "GDOF/s PA diffusion apply p=2..8; CG time-to-1e-8 mixed/learned vs FP64"
 SWEEP = ((2, 155), (4, 78), (6, 52), (8, 40))  # (p, n): about 30 M DOFs each
-CG_VEC_BYTES_PER_DOF = 112  # FP64 PCG vector kernels per iteration: p.Ap 16, x/r update 56, p update 40
+CG_VEC_BYTES_PER_DOF = 104  # FP64 PCG vector kernels per iteration: p.Ap 16, r update 32, x/p update 56
 
 # the translation unit of the apply kernels (its own sources and the build flags)
-APPLY_SOURCES = ("csrc/k_apply.hip", "csrc/apply_passes.h", "csrc/apply_common.h", "csrc/internal.h",
-                 "../include/hexpa.h", "build.py")
+APPLY_SOURCES = ("csrc/k_apply.hip", "csrc/apply_passes.h", "csrc/apply_common.h", "csrc/apply_chain.h",
+                 "csrc/apply_pencil.h", "csrc/internal.h", "../include/hexpa.h", "build.py")
 
 
 def kernel_source_hash():
