@@ -32,7 +32,9 @@
 // time in its chain of passes and 2-3 % waiting for memory.  At about 30 M DOFs (Q = p + 2;
 // p = 5 / 6 / 7 / 8, kernel alone): diffusion 1556 / 1073 / 1193 / 1186 -> 1227 / 918 / 1161 /
 // 1122 us, mass (MFMA) 746 / 508 / 544 / 566 -> 452 / 390 / 461 / 457, both 1744 / 1237 / 1552 /
-// 1752 -> 1418 / 1027 / 1353 / 1272.  What bounds it now: at p = 6 memory (4.6 TB/s; without
+// 1752 -> 1418 / 1027 / 1353 / 1272; with plain loads of D where its rows are not whole lines
+// diffusion at p = 5 / 7 / 8 1022 / 1035 / 1057 (all orders timed with both load kinds at
+// load_once).  What bounds it now: at p = 6 memory (4.6 TB/s; without
 // the scatter's atomics, which are carried out beyond the L2 request by request, 674 us, the
 // rate of a plain read), at p = 8 the chains (MFMA 41 %, LDS 45 % busy).
 #pragma once
@@ -74,6 +76,7 @@ struct ChainShape {
     // 2, 4, 6, 8: 977/585, 945/433, 919/392, 907/388, 904/422 us; at p = 8 with 2, 4, 6:
     // 1153/467, 1133/451, 1268/467 (LDS for a workgroup less).
     static constexpr int RUN = D >= 8 ? 4 : 6;
+    static constexpr bool WHOLE_LINES = !kDiff || Q2 % 16 == 0;  // (mass: no difference)
     static constexpr bool ok = D >= 6;
 };
 
@@ -185,7 +188,7 @@ __global__ __launch_bounds__((ChainShape<D, Q, OPS>::NT), (ChainShape<D, Q, OPS>
         for (int c = 0; c < NC; ++c)
 #pragma unroll
             for (int tc = 0; tc < TQ; ++tc)
-                dq[c][tc] = __builtin_nontemporal_load(p + c * Q3 + min(4 * tc + h, Q - 1) * Q2);
+                dq[c][tc] = load_once<S::WHOLE_LINES>(p + c * Q3 + min(4 * tc + h, Q - 1) * Q2);
     };
     // Scatter-add of a run's outputs.  A thread keeps its element and place i in the node row of
     // the run and walks the rows (j, k): a wave's atomics cover whole rows of the run, and each

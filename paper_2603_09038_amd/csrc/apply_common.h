@@ -127,6 +127,23 @@ __device__ __forceinline__ void row_node(int R, int &e, int &I)
     I = t - e * D + D * jk;
 }
 
+// One value of D, which a launch reads once.  Where the pieces that the waves read are whole
+// 128-byte lines (WHOLE) the load is non-temporal; otherwise two waves, or two loads of one,
+// share a line, and a non-temporal one is gone from the L2 before its second half is asked for
+// (diffusion at about 30 M DOFs, non-temporal -> plain: p = 8, Q = 10 1131 -> 1057 us, p = 7,
+// Q = 9 1165 -> 1035, p = 6, Q = 7 831 -> 772, p = 5, Q = 7 1112 -> 1022, p = 4, Q = 5 930 -> 858,
+// p = 2, Q = 3 1402 -> 1321, p = 1, Q = 3 2428 -> 2195; whole lines, p = 6, Q = 8: 923 -> 961, so
+// non-temporal there).  The mass operator's one value a point makes no difference or loses
+// (p = 4, Q = 6 469 -> 483), nor did the mixed operator gain (p = 4 408 -> 416).
+template <bool WHOLE, class T>
+__device__ __forceinline__ T load_once(const T *p)
+{
+    if constexpr (WHOLE)
+        return __builtin_nontemporal_load(p);
+    else
+        return *p;
+}
+
 // ------------------------------------------------------------------ table accessors
 __device__ __forceinline__ double tB(const DevTables *t, int a, int i, int D) { return t->B[a * D + i]; }
 __device__ __forceinline__ double tG(const DevTables *t, int a, int i, int D) { return t->G[a * D + i]; }

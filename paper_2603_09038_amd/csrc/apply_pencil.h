@@ -43,6 +43,8 @@ struct PencilShape {
     static constexpr int NM = (E * D3 + NT - 1) / NT;  // nodes per thread
     // waves per SIMD the registers are limited for; the sixth and seventh D value spill at p = 4
     static constexpr int MINW = NC == 7 && D == 5 ? 2 : 3;
+    // (mass at p = 4, Q = 6: 469 us with non-temporal loads, 483 without)
+    static constexpr bool WHOLE_LINES = !kDiff || Q2 % 16 == 0;
     // Where it is the faster one.  With Q = p + 2 a thread of diffusion holds 6 (p + 2) D values
     // for its pencil against 6 (p + 2)^3 E / NT in the pass-by-pass kernel, which then keeps more
     // waves resident (p = 1 / 2 / 3 / 4: 2430 / 1381 / 1126 / 725 there, 2748 / 1390 / 1175 / 763
@@ -88,7 +90,7 @@ __global__ __launch_bounds__((PencilShape<D, Q, OPS>::NT), (PencilShape<D, Q, OP
 #pragma unroll
         for (int c = 0; c < NC; ++c)
 #pragma unroll
-            for (int z = 0; z < Q; ++z) dq[c][z] = __builtin_nontemporal_load(p + c * Q3 + z * Q2);
+            for (int z = 0; z < Q; ++z) dq[c][z] = load_once<S::WHOLE_LINES>(p + c * Q3 + z * Q2);
     };
     // maps and x in row order (node row, element, i): consecutive DOFs of a group's neighbours
     auto load_map = [&](int32_t (&m)[NM], int gg) {

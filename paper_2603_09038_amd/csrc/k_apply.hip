@@ -114,8 +114,10 @@ __device__ __forceinline__ void load_qdata(T (&dq)[S::NS][S::NCOMP], const T *__
         const bool ok = e < nv;
         const int64_t ge = ok ? (EL ? elist[e0 + e] : e0 + e) : 0;
         const T *src = qd + ge * (int64_t)(S::NCOMP * S::Q3) + r;
+        // split lines are few when a component is two waves long (p = 4, Q = 6: 1370 us, 1385 plain)
+        constexpr bool WHOLE = !S::kDiff || S::Q3 * sizeof(T) % 128 == 0 || S::Q3 >= 128;
 #pragma unroll
-        for (int c = 0; c < S::NCOMP; ++c) dq[s][c] = ok ? __builtin_nontemporal_load(src + c * S::Q3) : T(0);
+        for (int c = 0; c < S::NCOMP; ++c) dq[s][c] = ok ? load_once<WHOLE>(src + c * S::Q3) : T(0);
     }
 }
 
