@@ -1,8 +1,8 @@
 // FP32 forward and backward of the learned preconditioner's network (training, and the FP32
 // inference option): three 3x3x3 cross-correlations (zero padding 1, bias) on the (p+1)^3
 // nodal tiles, 2 -> 16 -> 16 -> 1 channels with ReLU between, their input gradients, weight
-// gradients and the gather/scatter around them.  All arithmetic is FP32 (the weight-gradient
-// partial sums are added in FP64).
+// gradients and the gather/scatter around them.  All arithmetic is FP32, but for the
+// weight gradients' sums (see there).
 //
 // Sixteen tiles form a group: the tiles of +r of eight consecutive elements and the tiles of
 // -r of the same eight (tile t = 8 sign + element).  The 16-channel tensors are stored
@@ -367,11 +367,17 @@ __global__ __launch_bounds__(256, 4) void k_conv_out(int64_t ngroups, const floa
 
 // ------------------------------------------------------------------ weight gradients
 // dW[o][c][tap] = sum over tiles and points of dout[o][pt] in[c][pt + off(tap)]: an MFMA
-// takes four tiles as its k (lane l holds channel l%16) and adds a 16 x 16 block of one tap.  All
-// 27 taps' blocks stay in registers over every row a wave takes; the waves of a workgroup
-// are then added in wave order through LDS and the workgroup writes one row of `partial`
-// (weights, then biases), which the two reduction kernels add in a fixed order.
-// Layer 2, 32^3, p = 4: 2.46 -> 0.70 ms (the matrix pipe, as the convolutions).
+// takes four tiles as its k (lane l holds channel l%16) and adds a 16 x 16 block of one tap.
+// The blocks of a wave's taps (layer 2: the nine of its tap plane) stay in registers over every row it takes; the
+// waves of a workgroup are then added in FP64 in wave order through LDS and the workgroup writes one row of
+// `partial` (weights, then biases), which the two reduction kernels add in FP64 in a fixed order.
+// What is added in FP32 before that is short, since each addition rounds at the size of the
+// sum so far: layer 2 takes 4 N products an MFMA chain, adds the four chains of a row in a tree
+// and the rows one by one; layers 1 and 3 take eight products a chain and add a point's two
+// chains in FP32, all else in FP64.  (One chain over all products of a wave, 10,400 at 32^3,
+// left twice the rounding of the result, 5.4e-8 and at 48^3 9.2e-8; now 2.7e-8 and 2.9e-8, of
+// which 2.5e-8 is the rounding of the result to FP32.)
+// Layer 2, 32^3, p = 4: 2.46 -> 0.63 ms (the matrix pipe, as the convolutions).
 // The rows come as 16-byte loads (a vector memory instruction occupies the CU's address unit
 // for about 16 cycles whatever its width: with 4-byte loads in the layout the MFMA wants this
 // kernel took 1.02-1.22 ms) and are turned through wave-private LDS, a point's block at
@@ -407,13 +413,12 @@ __global__ __launch_bounds__(256, 2) void k_wgrad16(int64_t ngroups, const float
 {
     constexpr int NT = kNetW2 + kNetCh;
     constexpr int RED = 27 * 4 * 64, BUF = N * kTileGroup * 16;
-    __shared__ float sh[RED > kConvWaves * BUF ? RED : kConvWaves * BUF];  // row buffers, then the sums
-    __shared__ float redb[64];
-    float *red = sh;
+    __shared__ double red[RED > kConvWaves * BUF / 2 ? RED : kConvWaves * BUF / 2];  // row buffers, then the sums
+    __shared__ double redb[64];
     const int lane = threadIdx.x & 63, m = lane & 15;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    float *buf = sh + wave * BUF;
-    if (threadIdx.x < 64) redb[threadIdx.x] = 0.f;
+    float *buf = reinterpret_cast<float *>(red) + wave * BUF;
+    if (threadIdx.x < 64) redb[threadIdx.x] = 0.0;
     // This wave's tap plane tz: of each 3N - 2 consecutive waves of an XCD, N - 1, N and N - 1
     // take tz = 0, 1, 2, in proportion to the output planes a group has for it.  Its items are
     // those planes of the XCD's groups, round-robin over the waves of the same tz.
@@ -428,15 +433,29 @@ __global__ __launch_bounds__(256, 2) void k_wgrad16(int64_t ngroups, const float
 #pragma unroll
     for (int t = 0; t < 9; ++t) acc[t] = (f4_t){0.f, 0.f, 0.f, 0.f};
     float bacc = 0.f;
-    // one block of MFMAs: output row a, input row b, row tap ty
-    auto block = [&](const f4_t (&a)[N], const f4_t (&b)[N], f4_t *c) {
+    auto add = [](f4_t *c, const f4_t (&part)[3]) {
 #pragma unroll
-        for (int s = 0; s < 4; ++s)
+        for (int tx = 0; tx < 3; ++tx) {
+            c[tx] += part[tx];
+            asm volatile("" : "+v"(c[tx]));  // here: sunk to the next use, the parts would spill
+        }
+    };
+    // one block of MFMAs: output row a, input row b, row tap ty, in four parts of 4 N products
+    auto block = [&](const f4_t (&a)[N], const f4_t (&b)[N], f4_t *c) {
+        f4_t part[4][3];
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {
+#pragma unroll
+            for (int tx = 0; tx < 3; ++tx) part[s][tx] = (f4_t){0.f, 0.f, 0.f, 0.f};
 #pragma unroll
             for (int i = 0; i < N; ++i)
 #pragma unroll
                 for (int tx = 0; tx < 3; ++tx)
-                    if (i + tx - 1 >= 0 && i + tx - 1 < N) c[tx] = mfma4(a[i][s], b[i + tx - 1][s], c[tx]);
+                    if (i + tx - 1 >= 0 && i + tx - 1 < N) part[s][tx] = mfma4(a[i][s], b[i + tx - 1][s], part[s][tx]);
+            if (s & 1) add(part[s - 1], part[s]);
+        }
+        add(part[0], part[2]);
+        add(c, part[0]);
     };
     for (int64_t it = q * cnt + r - base; it < end; it += nw) {
         const int64_t g = g0 + it / cnt;
@@ -460,12 +479,15 @@ __global__ __launch_bounds__(256, 2) void k_wgrad16(int64_t ngroups, const float
             if (jp > 0) block(a[(jp + 2) % 3], b, acc + 6);
             block(a[jp % 3], b, acc + 3);
             if (jp + 1 < N) block(a[(jp + 1) % 3], b, acc);
-            if (tz == 1)
+            if (tz == 1) {
+                float bpart = 0.f;
 #pragma unroll
                 for (int i = 0; i < N; ++i) {
                     const f4_t v = a[jp % 3][i];
-                    bacc += (v[0] + v[1]) + (v[2] + v[3]);
+                    bpart += (v[0] + v[1]) + (v[2] + v[3]);
                 }
+                bacc += bpart;
+            }
             // the rows after the next: requested before the next ones are turned
             if (jp + 2 < N) load_raw<N>(rb[jp & 1], in, rin + jp + 2, lane);
             if (jp + 3 < N) load_raw<N>(ra[(jp + 1) & 1], dout, rout + jp + 3, lane);
@@ -475,7 +497,7 @@ __global__ __launch_bounds__(256, 2) void k_wgrad16(int64_t ngroups, const float
         }
     }
     __syncthreads();
-    for (int i = threadIdx.x; i < RED; i += 256) red[i] = 0.f;
+    for (int i = threadIdx.x; i < RED; i += 256) red[i] = 0.0;
     for (int p = 0; p < kConvWaves; ++p) {
         __syncthreads();
         if (wave == p) {
@@ -490,10 +512,10 @@ __global__ __launch_bounds__(256, 2) void k_wgrad16(int64_t ngroups, const float
     float *row = partial + (int64_t)blockIdx.x * NT;
     for (int i = threadIdx.x; i < 27 * 4 * 64; i += 256) {
         const int l = i & 63, v = (i >> 6) & 3, t = i >> 8;
-        row[((4 * (l >> 4) + v) * kNetCh + (l & 15)) * 27 + t] = red[i];
+        row[((4 * (l >> 4) + v) * kNetCh + (l & 15)) * 27 + t] = (float)red[i];
     }
     if (threadIdx.x < kNetCh)
-        row[kNetW2 + m] = (redb[m] + redb[m + 16]) + (redb[m + 32] + redb[m + 48]);
+        row[kNetW2 + m] = (float)((redb[m] + redb[m + 16]) + (redb[m + 32] + redb[m + 48]));
 }
 
 // Layers 1 and 3: one operand has 16 channels (`wide`: rows c = l%16), the other one or two
@@ -501,25 +523,24 @@ __global__ __launch_bounds__(256, 2) void k_wgrad16(int64_t ngroups, const float
 // tap col / C, channel col % C, read at the point shifted by that tap (zero outside the
 // tile).  Layer 1 (C = 2): wide = dout at pt, thin = in at pt + off.  Layer 3 (C = 1): wide =
 // in at q, thin = dout at q - off; its bias is the column of the centre tap summed.
-// Bound by the read of the wide operand.  32^3, p = 4: 0.491 -> 0.24 and 0.530 -> 0.16 ms.
+// Bound by the read of the wide operand.  32^3, p = 4: 0.491 -> 0.25 and 0.530 -> 0.17 ms.
 template <int N, int C>
 __global__ __launch_bounds__(256, 3) void k_wgrad_thin(int64_t ngroups, const float *__restrict__ wide,
                                                        const float *__restrict__ thin, float *__restrict__ partial)
 {
     constexpr int NCT = (27 * C + 15) / 16, NW = 27 * C * kNetCh, NT = NW + (C == 2 ? kNetCh : 1);
     constexpr int RED = NCT * 4 * 64, BUF = N * kTileGroup * 20;
-    __shared__ float sh[RED > kConvWaves * BUF ? RED : kConvWaves * BUF];  // row buffers, then the sums
-    __shared__ float redb[64];
-    float *red = sh;
+    __shared__ double red[RED > kConvWaves * BUF / 2 ? RED : kConvWaves * BUF / 2];  // row buffers, then the sums
+    __shared__ double redb[64];
     const int lane = threadIdx.x & 63, h = lane >> 4, m = lane & 15;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    float *buf = sh + wave * BUF;
-    f4_t acc[NCT];
+    float *buf = reinterpret_cast<float *>(red) + wave * BUF;
+    double acc[NCT][4];
     int off[NCT];               // shift of this lane's column, in floats of `thin`
     int mi[NCT], mj[NCT], mk[NCT];  // bit x: the shifted point of a point with that index is inside
 #pragma unroll
     for (int t = 0; t < NCT; ++t) {
-        acc[t] = (f4_t){0.f, 0.f, 0.f, 0.f};
+        acc[t][0] = acc[t][1] = acc[t][2] = acc[t][3] = 0.0;
         const int col = 16 * t + m, tap = col / C;
         const bool has = tap < 27;
         const int sg = C == 2 ? 1 : -1;
@@ -532,7 +553,7 @@ __global__ __launch_bounds__(256, 3) void k_wgrad_thin(int64_t ngroups, const fl
             if (has && (unsigned)(x + dz) < (unsigned)N) mk[t] |= 1 << x;
         }
     }
-    float bacc = 0.f;
+    double bacc = 0.0;
     RowWalk<N> w(ngroups, wave);
     for (; w.it < w.end; w.it += w.step) {
         int64_t g;
@@ -541,10 +562,7 @@ __global__ __launch_bounds__(256, 3) void k_wgrad_thin(int64_t ngroups, const fl
         f4_t a[N], raw[N];
         load_raw<N>(raw, wide, (g * N + k) * N + j, lane);
         turn_row<N, 20>(a, raw, buf, lane);
-        f4_t part[NCT];  // this row's sums: short chains round less
         float bpart = 0.f;
-#pragma unroll
-        for (int t = 0; t < NCT; ++t) part[t] = (f4_t){0.f, 0.f, 0.f, 0.f};
         const float *p = thin + ((g * N + k) * N + j) * (int64_t)(N * C * kTileGroup) + 4 * h;
 #pragma unroll
         for (int i = 0; i < N; ++i) {
@@ -555,16 +573,23 @@ __global__ __launch_bounds__(256, 3) void k_wgrad_thin(int64_t ngroups, const fl
                 const f4_t v = *reinterpret_cast<const f4_t *>(p + i * (C * kTileGroup) + (ok ? off[t] : 0));
                 b[t] = ok ? v : (f4_t){0.f, 0.f, 0.f, 0.f};
             }
+            // a point's sixteen products in two chains of eight
 #pragma unroll
-            for (int s = 0; s < 4; ++s)
+            for (int t = 0; t < NCT; ++t) {
+                f4_t u = mfma4(a[i][0], b[t][0], (f4_t){0.f, 0.f, 0.f, 0.f});
+                f4_t v = mfma4(a[i][1], b[t][1], (f4_t){0.f, 0.f, 0.f, 0.f});
+                u = mfma4(a[i][2], b[t][2], u);
+                v = mfma4(a[i][3], b[t][3], v);
 #pragma unroll
-                for (int t = 0; t < NCT; ++t) part[t] = mfma4(a[i][s], b[t][s], part[t]);
+                for (int x = 0; x < 4; ++x) {
+                    acc[t][x] += (double)(u[x] + v[x]);
+                    asm volatile("" : "+v"(acc[t][x]));  // here: not sunk behind the other points' MFMAs
+                }
+            }
             if (C == 2) bpart += (a[i][0] + a[i][1]) + (a[i][2] + a[i][3]);
             else bpart += (b[0][0] + b[0][1]) + (b[0][2] + b[0][3]);  // column m = 13: the centre tap
         }
-#pragma unroll
-        for (int t = 0; t < NCT; ++t) acc[t] += part[t];
-        bacc += bpart;
+        bacc += (double)bpart;
     }
     __syncthreads();
     for (int q = 0; q < kConvWaves; ++q) {
@@ -583,12 +608,12 @@ __global__ __launch_bounds__(256, 3) void k_wgrad_thin(int64_t ngroups, const fl
     float *row = partial + (int64_t)blockIdx.x * NT;
     for (int i = threadIdx.x; i < NCT * 4 * 64; i += 256) {
         const int l = i & 63, v = (i >> 6) & 3, col = 16 * (i >> 8) + (l & 15), ch = 4 * (l >> 4) + v;
-        if (col < 27 * C) row[(ch * C + col % C) * 27 + col / C] = red[i];
+        if (col < 27 * C) row[(ch * C + col % C) * 27 + col / C] = (float)red[i];
     }
     if (C == 2) {
-        if (threadIdx.x < kNetCh) row[NW + m] = (redb[m] + redb[m + 16]) + (redb[m + 32] + redb[m + 48]);
+        if (threadIdx.x < kNetCh) row[NW + m] = (float)((redb[m] + redb[m + 16]) + (redb[m + 32] + redb[m + 48]));
     } else if (threadIdx.x == 0) {
-        row[NW] = (redb[13] + redb[13 + 16]) + (redb[13 + 32] + redb[13 + 48]);
+        row[NW] = (float)((redb[13] + redb[13 + 16]) + (redb[13 + 32] + redb[13 + 48]));
     }
 }
 
