@@ -281,16 +281,26 @@ int net_part(pa_lp *lp, const double *r, double *z, hipStream_t s, bool fp16, bo
     return PA_OK;
 }
 
+bool has_coarse_graph(const pa_lp *lp) { return lp->cexec && lp->cgraph_iters == lp->o.coarse_iters; }
+
+hipError_t coarse_solve(pa_lp *lp, hipStream_t s)
+{
+    return coarse_pcg(lp->box, lp->S, lp->cdinv, lp->cr, lp->cu, lp->cz, lp->cp0, lp->cp1, lp->cAp, lp->cpart, lp->csc,
+                      lp->o.coarse_iters, s);
+}
+
 // Capture the coarse Jacobi-PCG (2 kernels per iteration) into a graph so that one
 // launch replaces 2k + 1; the kernels clear what they need themselves (no memset nodes).
+// Called when a first application has queued all its kernels (its coarse solve one by one), so
+// that the host's capture runs behind them: before the network's 400 us of work, 32^3 at p = 4,
+// it left the GPU idle and the first application took 799 us instead of 639.
 int ensure_coarse_graph(pa_lp *lp)
 {
-    if (lp->cexec && lp->cgraph_iters == lp->o.coarse_iters) return PA_OK;
+    if (has_coarse_graph(lp)) return PA_OK;
     lp->free_graph();
     if (!lp->cap_stream) HIP_OK(hipStreamCreateWithFlags(&lp->cap_stream, hipStreamNonBlocking));
     HIP_OK(hipStreamBeginCapture(lp->cap_stream, hipStreamCaptureModeThreadLocal));
-    const hipError_t e1 = coarse_pcg(lp->box, lp->S, lp->cdinv, lp->cr, lp->cu, lp->cz, lp->cp0, lp->cp1, lp->cAp,
-                                     lp->cpart, lp->csc, lp->o.coarse_iters, lp->cap_stream);
+    const hipError_t e1 = coarse_solve(lp, lp->cap_stream);
     const hipError_t e2 = hipStreamEndCapture(lp->cap_stream, &lp->cgraph);
     HIP_OK(e1);
     HIP_OK(e2);
@@ -300,14 +310,13 @@ int ensure_coarse_graph(pa_lp *lp)
 }
 
 // z (+)= P1 A1^{-1} P1^T r, then zero on the essential DOFs; with m, z = m * r + P1 A1^{-1} P1^T r
-// and the essential DOFs are left to the caller
+// and the essential DOFs are left to the caller, who calls ensure_coarse_graph when all is queued
 int coarse_part(pa_lp *lp, const double *r, double *z, bool add, hipStream_t s, const double *m = nullptr)
 {
     HIP_OK(coarse_restrict(lp->box, lp->gll, r, lp->cr, lp->ct1, lp->ct2, s));
     if (lp->ncess) HIP_OK(vec_zero_list(lp->cr, lp->cess, lp->ncess, s));
-    int rc = ensure_coarse_graph(lp);
-    if (rc) return rc;
-    HIP_OK(hipGraphLaunch(lp->cexec, s));
+    if (has_coarse_graph(lp)) HIP_OK(hipGraphLaunch(lp->cexec, s));
+    else HIP_OK(coarse_solve(lp, s));
     HIP_OK(coarse_prolong(lp->box, lp->gll, lp->cu, z, add, m, r, s));
     if (!m && lp->op->ness) HIP_OK(vec_zero_list(z, lp->op->d_ess, lp->op->ness, s));
     return PA_OK;
@@ -440,10 +449,13 @@ int hexpa::lp_precondition(pa_lp *lp, const double *r, double *z, hipStream_t s)
     } else {
         HIP_OK(vec_mul(z, lp->dinv, r, lp->ndof, s));
     }
-    if (lp->o.use_net)  // clears the essential DOFs
-        return net_part(lp, r, z, s, lp->o.infer_fp16 != 0, true, lp->o.net_scale > 0.0 ? lp->o.net_scale : 1.0);
-    if (lp->op->ness) HIP_OK(vec_zero_list(z, lp->op->d_ess, lp->op->ness, s));
-    return PA_OK;
+    if (lp->o.use_net) {  // clears the essential DOFs
+        int rc = net_part(lp, r, z, s, lp->o.infer_fp16 != 0, true, lp->o.net_scale > 0.0 ? lp->o.net_scale : 1.0);
+        if (rc) return rc;
+    } else if (lp->op->ness) {
+        HIP_OK(vec_zero_list(z, lp->op->d_ess, lp->op->ness, s));
+    }
+    return lp->o.use_coarse ? ensure_coarse_graph(lp) : PA_OK;
 }
 
 pa_op *hexpa::lp_operator(const pa_lp *lp) { return lp->op; }
@@ -461,7 +473,8 @@ extern "C" int pa_lp_coarse(pa_lp *lp, const double *r, double *z, void *stream)
     PA_TRY
     if (!lp || !r || !z) return arg_error("pa_lp_coarse: NULL argument");
     if (lp->o.coarse_iters < 1) return arg_error("pa_lp_coarse: coarse_iters must be >= 1");
-    return coarse_part(lp, r, z, false, as_stream(stream));
+    int rc = coarse_part(lp, r, z, false, as_stream(stream));
+    return rc ? rc : ensure_coarse_graph(lp);
     PA_CATCH
 }
 
@@ -515,6 +528,7 @@ extern "C" int pa_lp_train_step(pa_lp *lp, const double *b, const double *xstar,
     if (rc) return rc;
     lp->step += 1;
     HIP_OK(nn_adam(lp->params, lp->grads, lp->adam_m, lp->adam_v, kNetParams, lp->o.lr, lp->step, s));
+    if (lp->o.use_coarse && (rc = ensure_coarse_graph(lp))) return rc;
     if (loss) {
         HIP_OK(hipMemcpyAsync(loss, lp->dsc + 2, sizeof(double), hipMemcpyDeviceToHost, s));
         HIP_OK(hipStreamSynchronize(s));
