@@ -283,6 +283,16 @@ int net_part(pa_lp *lp, const double *r, double *z, hipStream_t s, bool fp16, bo
 
 bool has_coarse_graph(const pa_lp *lp) { return lp->cexec && lp->cgraph_iters == lp->o.coarse_iters; }
 
+// Is the caller capturing s?  A graph launched into a capture runs at once instead of becoming
+// part of it, so the coarse solve goes there kernel by kernel.
+int is_capturing(hipStream_t s, bool *yes)
+{
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    if (s) HIP_OK(hipStreamIsCapturing(s, &st));  // the default stream cannot be captured
+    *yes = st == hipStreamCaptureStatusActive;
+    return PA_OK;
+}
+
 hipError_t coarse_solve(pa_lp *lp, hipStream_t s)
 {
     return coarse_pcg(lp->box, lp->S, lp->cdinv, lp->cr, lp->cu, lp->cz, lp->cp0, lp->cp1, lp->cAp, lp->cpart, lp->csc,
@@ -294,9 +304,12 @@ hipError_t coarse_solve(pa_lp *lp, hipStream_t s)
 // Called when a first application has queued all its kernels (its coarse solve one by one), so
 // that the host's capture runs behind them: before the network's 400 us of work, 32^3 at p = 4,
 // it left the GPU idle and the first application took 799 us instead of 639.
-int ensure_coarse_graph(pa_lp *lp)
+int ensure_coarse_graph(pa_lp *lp, hipStream_t s)
 {
     if (has_coarse_graph(lp)) return PA_OK;
+    bool cap;
+    int rc = is_capturing(s, &cap);
+    if (rc || cap) return rc;
     lp->free_graph();
     if (!lp->cap_stream) HIP_OK(hipStreamCreateWithFlags(&lp->cap_stream, hipStreamNonBlocking));
     HIP_OK(hipStreamBeginCapture(lp->cap_stream, hipStreamCaptureModeThreadLocal));
@@ -315,7 +328,10 @@ int coarse_part(pa_lp *lp, const double *r, double *z, bool add, hipStream_t s, 
 {
     HIP_OK(coarse_restrict(lp->box, lp->gll, r, lp->cr, lp->ct1, lp->ct2, s));
     if (lp->ncess) HIP_OK(vec_zero_list(lp->cr, lp->cess, lp->ncess, s));
-    if (has_coarse_graph(lp)) HIP_OK(hipGraphLaunch(lp->cexec, s));
+    bool cap;
+    int rc = is_capturing(s, &cap);
+    if (rc) return rc;
+    if (has_coarse_graph(lp) && !cap) HIP_OK(hipGraphLaunch(lp->cexec, s));
     else HIP_OK(coarse_solve(lp, s));
     HIP_OK(coarse_prolong(lp->box, lp->gll, lp->cu, z, add, m, r, s));
     if (!m && lp->op->ness) HIP_OK(vec_zero_list(z, lp->op->d_ess, lp->op->ness, s));
@@ -455,7 +471,7 @@ int hexpa::lp_precondition(pa_lp *lp, const double *r, double *z, hipStream_t s)
     } else if (lp->op->ness) {
         HIP_OK(vec_zero_list(z, lp->op->d_ess, lp->op->ness, s));
     }
-    return lp->o.use_coarse ? ensure_coarse_graph(lp) : PA_OK;
+    return lp->o.use_coarse ? ensure_coarse_graph(lp, s) : PA_OK;
 }
 
 pa_op *hexpa::lp_operator(const pa_lp *lp) { return lp->op; }
@@ -474,7 +490,7 @@ extern "C" int pa_lp_coarse(pa_lp *lp, const double *r, double *z, void *stream)
     if (!lp || !r || !z) return arg_error("pa_lp_coarse: NULL argument");
     if (lp->o.coarse_iters < 1) return arg_error("pa_lp_coarse: coarse_iters must be >= 1");
     int rc = coarse_part(lp, r, z, false, as_stream(stream));
-    return rc ? rc : ensure_coarse_graph(lp);
+    return rc ? rc : ensure_coarse_graph(lp, as_stream(stream));
     PA_CATCH
 }
 
@@ -528,7 +544,7 @@ extern "C" int pa_lp_train_step(pa_lp *lp, const double *b, const double *xstar,
     if (rc) return rc;
     lp->step += 1;
     HIP_OK(nn_adam(lp->params, lp->grads, lp->adam_m, lp->adam_v, kNetParams, lp->o.lr, lp->step, s));
-    if (lp->o.use_coarse && (rc = ensure_coarse_graph(lp))) return rc;
+    if (lp->o.use_coarse && (rc = ensure_coarse_graph(lp, s))) return rc;
     if (loss) {
         HIP_OK(hipMemcpyAsync(loss, lp->dsc + 2, sizeof(double), hipMemcpyDeviceToHost, s));
         HIP_OK(hipStreamSynchronize(s));

@@ -41,3 +41,31 @@ def test_first_and_later_applications_agree(p, n):
     lp.close()
     for op in ops:
         op.close()
+
+
+@pytest.mark.parametrize("used_before", [False, True])
+def test_application_in_a_captured_graph(used_before):
+    """An application that the caller captures is part of the graph, whether the handle has its
+    own graph already or not: replays on new residuals, with eager work between them."""
+    import torch
+    from paper_2603_09038_amd import hexpa as hx
+    op = hx.PAOperator(synth.box_mesh(4, perturb=0.1, seed=1), 2, 4, ops=hx.PA_DIFFUSION, ess_mode=1)
+    lp = hx.LearnedPreconditioner(op, use_net=False, use_coarse=True)
+    want = hx.LearnedPreconditioner(op, use_net=False, use_coarse=True)
+    r, z = (torch.zeros(op.ndof, dtype=torch.float64, device="cuda") for _ in range(2))
+    if used_before:
+        lp.apply(r, z)
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        lp.apply(r, z)
+    for seed in range(4):
+        r.copy_(torch.tensor(synth.rand_x(op.ndof, seed)))
+        z.fill_(np.nan)
+        g.replay()
+        ref = want.apply(r)
+        torch.cuda.synchronize()
+        # two handles: their stencils are summed by atomics
+        assert (z - ref).norm() <= 1e-9 * ref.norm()
+    for h in (lp, want, op):
+        h.close()
