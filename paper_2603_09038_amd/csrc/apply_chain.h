@@ -95,9 +95,13 @@ __global__ __launch_bounds__((ChainShape<D, Q, OPS>::NT), (ChainShape<D, Q, OPS>
     // operand is zero: everything there is finite when the element's values are, since all of
     // LDS is cleared once and the padding never written.
     constexpr int NT_ = S::NCH * CH + 4 * PB, NX = D * SX + 4 * PD;
-    constexpr int RUN = S::RUN;
+    // Elements of one colour share no DOFs: nothing to merge, so their runs have one element and
+    // each thread adds its own nodes to y, whose values it asked for when the element began.
+    // (Through the run's scatter a sixth to a quarter of the threads waited for a load of y in
+    // each of their rows.)
+    constexpr int RUN = ATOMIC ? S::RUN : 1;
     __shared__ double T[NT_], X[NX], Y[RUN * D3], tb[4 * TQ * PT], tg[DF ? 4 * TQ * PT : 1];
-    __shared__ int32_t lmap[RUN * D3];
+    __shared__ int32_t lmap[ATOMIC ? RUN * D3 : 1];
     const int tid = threadIdx.x, lane = tid & 63, h = lane >> 4, r = lane & 3, beta = (lane >> 2) & 3;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     auto barrier = [] { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); };  // LDS traffic only
@@ -206,10 +210,7 @@ __global__ __launch_bounds__((ChainShape<D, Q, OPS>::NT), (ChainShape<D, Q, OPS>
             if (i == 0 && e > 0 && lmap[L - D3 + (D - 1)] == gi) continue;  // added by the left neighbour
             double v = Y[L];
             if (i == D - 1 && e + 1 < RUN && lmap[L + D3 - (D - 1)] == gi) v += Y[L + D3 - (D - 1)];
-            if (ATOMIC)
-                unsafeAtomicAdd(y + gi, v);
-            else
-                y[gi] += v;
+            unsafeAtomicAdd(y + gi, v);
         }
     };
     // maps of this element, the next and the one after it; past the last one a workgroup loads
@@ -222,7 +223,8 @@ __global__ __launch_bounds__((ChainShape<D, Q, OPS>::NT), (ChainShape<D, Q, OPS>
     load_map(m1, nxt);
     load_d(cur);
     gather(xv, m0);
-    for (int i = tid; i < RUN * D3; i += NT) lmap[i] = -1;
+    if constexpr (ATOMIC)
+        for (int i = tid; i < RUN * D3; i += NT) lmap[i] = -1;
     barrier();  // basis tables
     if constexpr (S::WHOLE) {
 #pragma unroll
@@ -255,8 +257,13 @@ __global__ __launch_bounds__((ChainShape<D, Q, OPS>::NT), (ChainShape<D, Q, OPS>
         gather(xv, m1);
         int32_t m2[NS];
         load_map(m2, nx2);
+        double yv[NS];
+        if constexpr (!ATOMIC)
+#pragma unroll
+            for (int s = 0; s < NS; ++s) yv[s] = y[m0[s]];
         __builtin_amdgcn_sched_barrier(0);
-        if (full) scatter();
+        if constexpr (ATOMIC)
+            if (full) scatter();
         if (fwd) {
             double pb[TD], pg[DF ? TD : 1];
             const double *Xp = X + pfc * SX + r * PD + h;
@@ -296,7 +303,7 @@ __global__ __launch_bounds__((ChainShape<D, Q, OPS>::NT), (ChainShape<D, Q, OPS>
         // the scatter has read the map of the run before
 #pragma unroll
         for (int s = 0; s < NS; ++s)
-            if (tid + NT * s < D3) {
+            if (ATOMIC && tid + NT * s < D3) {
                 lmap[at * D3 + tid + NT * s] = m0[s];
                 if (full)
                     for (int e = 1; e < RUN; ++e) lmap[e * D3 + tid + NT * s] = -1;
@@ -396,6 +403,10 @@ __global__ __launch_bounds__((ChainShape<D, Q, OPS>::NT), (ChainShape<D, Q, OPS>
         }
         stage(xv);
         barrier();
+        if constexpr (!ATOMIC)
+#pragma unroll
+            for (int s = 0; s < NS; ++s)
+                if (tid + NT * s < D3) y[m0[s]] = yv[s] + Y[tid + NT * s];
         full = g1 != gc || nxt < 0;  // the run ends here
         if (nxt < 0) break;
         at = full ? 0 : at + 1;
@@ -409,7 +420,7 @@ __global__ __launch_bounds__((ChainShape<D, Q, OPS>::NT), (ChainShape<D, Q, OPS>
             m1[s] = m2[s];
         }
     }
-    scatter();
+    if constexpr (ATOMIC) scatter();
 }
 
 }  // namespace hexpa

@@ -802,7 +802,7 @@ static hipError_t launch_k(const pa_op *op, const typename ExT<EX>::T *qd, const
     if constexpr (EX == EX_MFMA64 && ChainShape<D, Q, OPS>::ok) {  // FP64 MFMA at p >= 5
         if (n == 0) return hipSuccess;
         constexpr auto kern = k_apply_chain<D, Q, OPS, ATOMIC>;
-        constexpr int NT = ChainShape<D, Q, OPS>::NT, RUN = ChainShape<D, Q, OPS>::RUN;
+        constexpr int NT = ChainShape<D, Q, OPS>::NT, RUN = ATOMIC ? ChainShape<D, Q, OPS>::RUN : 1;
         // runs as long as leaves every resident workgroup a few
         const int cap = capped(op, persistent_blocks<kern>(NT, n)), run = std::max(1, std::min(RUN, n / (2 * cap)));
         hipLaunchKernelGGL(kern, dim3(std::min(cap, (n + run - 1) / run)), dim3(NT), 0, s, n, run, elist,
