@@ -98,7 +98,8 @@ __global__ __launch_bounds__((ChainShape<D, Q, OPS>::NT), (ChainShape<D, Q, OPS>
     // Elements of one colour share no DOFs: nothing to merge, so their runs have one element and
     // each thread adds its own nodes to y, whose values it asked for when the element began.
     // (Through the run's scatter a sixth to a quarter of the threads waited for a load of y in
-    // each of their rows.)
+    // each of their rows.  All eight colours, us: mass p = 7, Q = 9, 25^3 202 -> 129, diffusion
+    // p = 8, Q = 10, 22^3 349 -> 288, p = 7, Q = 9, 25^3 321 -> 262; pass by pass 142, 313, 281.)
     constexpr int RUN = ATOMIC ? S::RUN : 1;
     __shared__ double T[NT_], X[NX], Y[RUN * D3], tb[4 * TQ * PT], tg[DF ? 4 * TQ * PT : 1];
     __shared__ int32_t lmap[ATOMIC ? RUN * D3 : 1];
