@@ -76,11 +76,32 @@ struct ChainShape {
     // 2, 4, 6, 8: 977/585, 945/433, 919/392, 907/388, 904/422 us; at p = 8 with 2, 4, 6:
     // 1153/467, 1133/451, 1268/467 (LDS for a workgroup less).
     static constexpr int RUN = D >= 8 ? 4 : 6;
+    // The run length for `each` elements a resident workgroup.  Runs save atomics but leave
+    // workgroups without work where there are few, and their LDS costs residency; a run of one
+    // is the kernel without them.  us with 1 / 2 / 3 / RUN elements (each in brackets):
+    //   mass, p = 6, Q = 7: 14^3 (2) 15.2 / 15.4 / 16.4 / 19.6, 16^3 (3) 20.2 / 17.3 / 18.2 / 22.4,
+    //   25^3 (12) 66.4 / 55.9 / 49.5 / 46.8, p = 5, Q = 6: 20^3 (5) 25.6 / 21.3 / 21.0 / 22.3 (19.8
+    //   with four);
+    //   diffusion, p = 7, Q = 8: 14^3 (3) 22.8 / 23.0 / 22.4 / 24.5, 15^3 (4) 28.1 / 25.3 / 26.1 /
+    //   27.4, 21^3 (12) 64.3 / 61.6 / 59.5 / 59.9;
+    //   where the basis operands come from LDS (not WHOLE) the halved LDS of the kernel without
+    //   runs counts more.  Mass, p = 7, Q = 9: 13^3 (2) 15.8 / 19.6 / 18.4 / 21.3, 19^3 (6) 41.3 /
+    //   48.1 / 45.0 / 37.1; diffusion, p = 8, Q = 10: 18^3 (11) 96.5 / 109 / 106 / 107, 22^3 (20)
+    //   178 / 187 / 185 / 184, 27^3 (38) 343 / - / 338 / 337, p = 7, Q = 9, 45^3 (177) 1066 / - /
+    //   1044 / 1025; both, p = 8, Q = 9: 22^3 178 / 194 / 191 / 192, 40^3 (125) 1030 / - / - / 998,
+    //   Q = 10, whose runs spill registers: 22^3 202 / 226 / 227 / 227, 40^3 1189 / - / - / 1209.
+    static constexpr int run_of(int each)
+    {
+        if (!WHOLE) return (kDiff ? each < 32 || (kMass && Q == 10) : each < 5) ? 1 : RUN;
+        const int r = kDiff ? each / 2 : each < 5 ? (each < 3 ? each : 3) : cmax(each / 2, 4);
+        return r < 1 ? 1 : r < RUN ? r : RUN;
+    }
     static constexpr bool WHOLE_LINES = !kDiff || Q2 % 16 == 0;  // (mass: no difference)
     static constexpr bool ok = D >= 6;
 };
 
-template <int D, int Q, int OPS, bool ATOMIC>
+// RUNS: runs of up to S::RUN elements (atomic scatter); else of one.
+template <int D, int Q, int OPS, bool ATOMIC, bool RUNS>
 __global__ __launch_bounds__((ChainShape<D, Q, OPS>::NT), (ChainShape<D, Q, OPS>::MINW)) void k_apply_chain(
     int n, int run, const int32_t *__restrict__ elist, const int32_t *__restrict__ emap, const double *__restrict__ qd,
     const DevTables *__restrict__ tab, const double *__restrict__ x, double *__restrict__ y)
@@ -95,14 +116,16 @@ __global__ __launch_bounds__((ChainShape<D, Q, OPS>::NT), (ChainShape<D, Q, OPS>
     // operand is zero: everything there is finite when the element's values are, since all of
     // LDS is cleared once and the padding never written.
     constexpr int NT_ = S::NCH * CH + 4 * PB, NX = D * SX + 4 * PD;
-    // Elements of one colour share no DOFs: nothing to merge, so their runs have one element and
-    // each thread adds its own nodes to y, whose values it asked for when the element began.
-    // (Through the run's scatter a sixth to a quarter of the threads waited for a load of y in
-    // each of their rows.  All eight colours, us: mass p = 7, Q = 9, 25^3 202 -> 129, diffusion
-    // p = 8, Q = 10, 22^3 349 -> 288, p = 7, Q = 9, 25^3 321 -> 262; pass by pass 142, 313, 281.)
-    constexpr int RUN = ATOMIC ? S::RUN : 1;
+    // Without runs (few elements a workgroup, and all coloured launches: elements of one colour
+    // share no DOFs) there is nothing to merge: each thread adds its own nodes to y, coloured
+    // with a load of y asked for when the element began.  (Through the runs' scatter most threads
+    // idled while the others walked the rows, coloured with a load of y to wait for in each.
+    // Coloured, all eight launches, us: mass p = 7, Q = 9, 25^3 202 -> 129, diffusion p = 8,
+    // Q = 10, 22^3 349 -> 288, p = 7, Q = 9, 25^3 321 -> 262; pass by pass 142, 313, 281.)
+    static_assert(ATOMIC || !RUNS, "runs merge by atomics");
+    constexpr int RUN = RUNS ? S::RUN : 1;
     __shared__ double T[NT_], X[NX], Y[RUN * D3], tb[4 * TQ * PT], tg[DF ? 4 * TQ * PT : 1];
-    __shared__ int32_t lmap[ATOMIC ? RUN * D3 : 1];
+    __shared__ int32_t lmap[RUNS ? RUN * D3 : 1];
     const int tid = threadIdx.x, lane = tid & 63, h = lane >> 4, r = lane & 3, beta = (lane >> 2) & 3;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     auto barrier = [] { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); };  // LDS traffic only
@@ -224,7 +247,7 @@ __global__ __launch_bounds__((ChainShape<D, Q, OPS>::NT), (ChainShape<D, Q, OPS>
     load_map(m1, nxt);
     load_d(cur);
     gather(xv, m0);
-    if constexpr (ATOMIC)
+    if constexpr (RUNS)
         for (int i = tid; i < RUN * D3; i += NT) lmap[i] = -1;
     barrier();  // basis tables
     if constexpr (S::WHOLE) {
@@ -263,7 +286,7 @@ __global__ __launch_bounds__((ChainShape<D, Q, OPS>::NT), (ChainShape<D, Q, OPS>
 #pragma unroll
             for (int s = 0; s < NS; ++s) yv[s] = y[m0[s]];
         __builtin_amdgcn_sched_barrier(0);
-        if constexpr (ATOMIC)
+        if constexpr (RUNS)
             if (full) scatter();
         if (fwd) {
             double pb[TD], pg[DF ? TD : 1];
@@ -304,7 +327,7 @@ __global__ __launch_bounds__((ChainShape<D, Q, OPS>::NT), (ChainShape<D, Q, OPS>
         // the scatter has read the map of the run before
 #pragma unroll
         for (int s = 0; s < NS; ++s)
-            if (ATOMIC && tid + NT * s < D3) {
+            if (RUNS && tid + NT * s < D3) {
                 lmap[at * D3 + tid + NT * s] = m0[s];
                 if (full)
                     for (int e = 1; e < RUN; ++e) lmap[e * D3 + tid + NT * s] = -1;
@@ -404,10 +427,14 @@ __global__ __launch_bounds__((ChainShape<D, Q, OPS>::NT), (ChainShape<D, Q, OPS>
         }
         stage(xv);
         barrier();
-        if constexpr (!ATOMIC)
+        if constexpr (!RUNS)
 #pragma unroll
             for (int s = 0; s < NS; ++s)
-                if (tid + NT * s < D3) y[m0[s]] = yv[s] + Y[tid + NT * s];
+                if (tid + NT * s < D3) {
+                    const double v = Y[tid + NT * s];
+                    if constexpr (ATOMIC) unsafeAtomicAdd(y + m0[s], v);
+                    else y[m0[s]] = yv[s] + v;
+                }
         full = g1 != gc || nxt < 0;  // the run ends here
         if (nxt < 0) break;
         at = full ? 0 : at + 1;
@@ -421,7 +448,7 @@ __global__ __launch_bounds__((ChainShape<D, Q, OPS>::NT), (ChainShape<D, Q, OPS>
             m1[s] = m2[s];
         }
     }
-    if constexpr (ATOMIC) scatter();
+    if constexpr (RUNS) scatter();
 }
 
 }  // namespace hexpa

@@ -801,12 +801,21 @@ static hipError_t launch_k(const pa_op *op, const typename ExT<EX>::T *qd, const
 {
     if constexpr (EX == EX_MFMA64 && ChainShape<D, Q, OPS>::ok) {  // FP64 MFMA at p >= 5
         if (n == 0) return hipSuccess;
-        constexpr auto kern = k_apply_chain<D, Q, OPS, ATOMIC>;
-        constexpr int NT = ChainShape<D, Q, OPS>::NT, RUN = ATOMIC ? ChainShape<D, Q, OPS>::RUN : 1;
-        // runs as long as leaves every resident workgroup a few
-        const int cap = capped(op, persistent_blocks<kern>(NT, n)), run = std::max(1, std::min(RUN, n / (2 * cap)));
-        hipLaunchKernelGGL(kern, dim3(std::min(cap, (n + run - 1) / run)), dim3(NT), 0, s, n, run, elist,
-                           op->d_elem_dofs, qd, op->d_tab, x, y);
+        using S = ChainShape<D, Q, OPS>;
+        auto launch = [&](auto kern, int cap, int run) {
+            hipLaunchKernelGGL(kern, dim3(std::min(cap, (n + run - 1) / run)), dim3(S::NT), 0, s, n, run, elist,
+                               op->d_elem_dofs, qd, op->d_tab, x, y);
+        };
+        if constexpr (ATOMIC) {
+            constexpr auto kern = k_apply_chain<D, Q, OPS, true, true>;
+            const int cap = capped(op, persistent_blocks<kern>(S::NT, n)), run = S::run_of(n / cap);
+            if (run > 1) {
+                launch(kern, cap, run);
+                return hipGetLastError();
+            }
+        }
+        constexpr auto kern = k_apply_chain<D, Q, OPS, ATOMIC, false>;
+        launch(kern, capped(op, persistent_blocks<kern>(S::NT, n)), 1);
         return hipGetLastError();
     } else if constexpr (EX == EX_VALU64 && ATOMIC && PencilShape<D, Q, OPS>::ok) {  // FP64 vector ALU, z in registers
         using S = PencilShape<D, Q, OPS>;
