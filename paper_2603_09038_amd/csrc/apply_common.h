@@ -134,7 +134,12 @@ __device__ __forceinline__ void row_node(int R, int &e, int &I)
 // Q = 9 1165 -> 1035, p = 6, Q = 7 831 -> 772, p = 5, Q = 7 1112 -> 1022, p = 4, Q = 5 930 -> 858,
 // p = 2, Q = 3 1402 -> 1321, p = 1, Q = 3 2428 -> 2195; whole lines, p = 6, Q = 8: 923 -> 961, so
 // non-temporal there).  The mass operator's one value a point makes no difference or loses
-// (p = 4, Q = 6 469 -> 483), nor did the mixed operator gain (p = 4 408 -> 416).
+// (p = 4, Q = 6 469 -> 483), nor did the mixed operator gain (p = 4 408 -> 416), nor does
+// k_apply_dma, whose threads walk a component in order (vector ALU and 16 bit, p = 5 to 8: within
+// 2 % either way).  It is even at p = 3, Q = 5, whose 125 values split one line in eight:
+// diffusion 20^3 16.6 -> 18.0, 30^3 47.9 -> 44.8 (D then stays in the memory-side cache), 50^3
+// 189 -> 196, 100^3 1528 -> 1513; with the mass term 19.6 -> 20.0, 55.2 -> 50.0, 221 -> 227,
+// 1834 -> 1831.
 template <bool WHOLE, class T>
 __device__ __forceinline__ T load_once(const T *p)
 {

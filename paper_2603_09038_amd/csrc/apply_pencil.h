@@ -50,7 +50,9 @@ struct PencilShape {
     // waves resident (p = 1 / 2 / 3 / 4: 2430 / 1381 / 1126 / 725 there, 2748 / 1390 / 1175 / 763
     // here), and so at p <= 2 with Q = p + 1 (805 / 801 and 1055 / 879); with the mass term the
     // pass-by-pass kernel has a fourth tensor and loses at p = 2, Q = 4, too.  Mass at p = 1 with
-    // Q = 3 is even (577 and 595).
+    // Q = 3 is even (577 and 595).  So is diffusion at p = 2, Q = 4 on smaller meshes, there and
+    // here: 24^3 12.0 and 13.1, 32^3 24.6 and 25.8, 50^3 85.0 and 81.5, 100^3 640 and 625, 155^3
+    // 2468 and 2534.
     static constexpr bool ok =
         D <= 5 && (kDiff ? (Q == D && D >= 4) || (kMass && D == 3 && Q == 4) : D >= 3 || Q == D);
 };

@@ -114,7 +114,10 @@ __device__ __forceinline__ void load_qdata(T (&dq)[S::NS][S::NCOMP], const T *__
         const bool ok = e < nv;
         const int64_t ge = ok ? (EL ? elist[e0 + e] : e0 + e) : 0;
         const T *src = qd + ge * (int64_t)(S::NCOMP * S::Q3) + r;
-        // split lines are few when a component is two waves long (p = 4, Q = 6: 1370 us, 1385 plain)
+        // split lines are few when a component is over two waves long (p = 4, Q = 6, us, the other
+        // way plain: diffusion 15^3 15 and 17, 35^3 118 and 121, 60^3 579 and 590, 78^3 1370 and
+        // 1385; with the mass term 17 and 18, 148 and 153, 706 and 716; where D just fits the
+        // memory-side cache, 25^3, 48 and 45, 57 and 55)
         constexpr bool WHOLE = !S::kDiff || S::Q3 * sizeof(T) % 128 == 0 || S::Q3 >= 128;
 #pragma unroll
         for (int c = 0; c < S::NCOMP; ++c) dq[s][c] = ok ? load_once<WHOLE>(src + c * S::Q3) : T(0);
@@ -457,9 +460,9 @@ __global__ __launch_bounds__(256) void k_dstep(int64_t npts, const T *__restrict
 //   forward passes | wait, D-step | issue D(g+1) | transposed passes and scatter.
 // So the D stream of the next group overlaps the transposed passes and the forward
 // passes, and the gathers overlap the forward passes, without holding registers.
-// (FP64 with MFMA contractions runs the chained kernel at these orders; this one serves the
-// vector-ALU and the 16-bit executors, and the mass operator at p = 4 but with the vector ALU,
-// which has the pencil kernel there.)
+// At these orders FP64 with MFMA contractions runs the chained kernel; this one serves the
+// vector-ALU and the 16-bit executors, and at p = 4 the mass operator alone with any executor but
+// the vector ALU (which runs the pencil kernel).
 constexpr int kDmaMinD = 6;                // orders p >= 5 (measured faster there; diffusion at p <= 4 keeps the register kernel)
 constexpr int kDmaLdsBudget = 53 * 1024;   // LDS bytes per workgroup of the DMA kernel
 
