@@ -60,9 +60,9 @@ constexpr int kCoarsePartials = 2048;  // partial sums of r.z and of p.Ap, at mo
 struct BoxDims {
     int nx, ny, nz, p;
 };
-// uf (+)= P1 u1: nodal interpolation of the p=1 field at the fine GLL nodes; with m1, uf = m1 * m2 + P1 u1.
-hipError_t coarse_prolong(const BoxDims &b, const double *gll, const double *u1, double *uf, bool add,
-                          const double *m1, const double *m2, hipStream_t s);
+// uf = P1 u1: nodal interpolation of the p=1 field at the fine GLL nodes; with m1, uf = m1 * m2 + P1 u1.
+hipError_t coarse_prolong(const BoxDims &b, const double *gll, const double *u1, double *uf, const double *m1,
+                          const double *m2, hipStream_t s);
 // r1 = P1^T rf (three separable 1-D passes, fixed summation order); t1, t2 are work arrays
 // of (nx+1)(ny p+1)(nz p+1) and (nx+1)(ny+1)(nz p+1) values.
 hipError_t coarse_restrict(const BoxDims &b, const double *gll, const double *rf, double *r1, double *t1, double *t2,

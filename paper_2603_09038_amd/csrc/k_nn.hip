@@ -68,19 +68,17 @@ __global__ void k_loss_scale(double *g, int64_t n, double *sc)
 }
 
 // ---------------------------------------------------------------- coarse level
-// uf = P1 u1, plus uf or m1 * m2 where given.  Bound by memory; 32-bit indexes (a lattice has
+// uf = P1 u1, plus m1 * m2 where given.  Bound by memory; 32-bit indexes (a lattice has
 // fewer than 2^31 points) since 64-bit divisions by run-time sizes cost more than the traffic:
 // 129^3 points, with the product 18.4 us; the product 9.4 and the sum 16.9 before.
-enum { PROLONG_SET, PROLONG_ADD, PROLONG_MUL };
 __global__ void k_prolong(BoxDims b, const double *__restrict__ gll, const double *__restrict__ u1,
-                          double *__restrict__ uf, int mode, const double *__restrict__ m1,
-                          const double *__restrict__ m2)
+                          double *__restrict__ uf, const double *__restrict__ m1, const double *__restrict__ m2)
 {
     const uint32_t p = b.p, Mx = b.nx * p + 1, My = b.ny * p + 1, Mz = b.nz * p + 1;
     const uint32_t Cx = b.nx + 1, Cy = b.ny + 1;
     const uint32_t g = blockIdx.x * blockDim.x + threadIdx.x;
     if (g >= Mx * My * Mz) return;
-    const double base = mode == PROLONG_ADD ? uf[g] : mode == PROLONG_MUL ? m1[g] * m2[g] : 0.0;
+    const double base = m1 ? m1[g] * m2[g] : 0.0;
     const uint32_t K = g / (Mx * My), R = g - K * (Mx * My), J = R / Mx, I = R - J * Mx;
     const uint32_t ex = min(I / p, (uint32_t)b.nx - 1), ey = min(J / p, (uint32_t)b.ny - 1),
                    ez = min(K / p, (uint32_t)b.nz - 1);
@@ -92,7 +90,7 @@ __global__ void k_prolong(BoxDims b, const double *__restrict__ gll, const doubl
         const double w = (ca ? x : 1.0 - x) * (cb ? y : 1.0 - y) * (cc ? z : 1.0 - z);
         v += w * u1[(ex + ca) + Cx * ((ey + cb) + Cy * (ez + cc))];
     }
-    uf[g] = mode == PROLONG_SET ? v : base + v;
+    uf[g] = m1 ? base + v : v;
 }
 
 // Restriction r1 = P1^T rf, separable: the weight of fine node (I,J,K) at coarse vertex
@@ -582,12 +580,11 @@ hipError_t vec_loss_scale(double *g, int64_t n, double *sc, hipStream_t s)
     return hipGetLastError();
 }
 
-hipError_t coarse_prolong(const BoxDims &b, const double *gll, const double *u1, double *uf, bool add,
-                          const double *m1, const double *m2, hipStream_t s)
+hipError_t coarse_prolong(const BoxDims &b, const double *gll, const double *u1, double *uf, const double *m1,
+                          const double *m2, hipStream_t s)
 {
     const int64_t nf = ((int64_t)b.nx * b.p + 1) * ((int64_t)b.ny * b.p + 1) * ((int64_t)b.nz * b.p + 1);
-    const int mode = m1 ? PROLONG_MUL : add ? PROLONG_ADD : PROLONG_SET;
-    hipLaunchKernelGGL(k_prolong, dim3(nblk(nf)), dim3(256), 0, s, b, gll, u1, uf, mode, m1, m2);
+    hipLaunchKernelGGL(k_prolong, dim3(nblk(nf)), dim3(256), 0, s, b, gll, u1, uf, m1, m2);
     return hipGetLastError();
 }
 

@@ -14,7 +14,6 @@ struct CgScalars {
 };
 
 hipError_t vec_fill(float *y, float v, int64_t n, hipStream_t s);
-hipError_t vec_set_list(float *y, float v, const int32_t *list, int n, hipStream_t s);
 hipError_t vec_recip(double *y, const double *x, int64_t n, hipStream_t s);
 hipError_t vec_to_f32(float *y, const double *x, double scale, int64_t n, hipStream_t s);  // y = (float)(x*scale)
 hipError_t vec_axpy_f32(double *x, double a, const float *d, int64_t n, hipStream_t s);    // x += a*d

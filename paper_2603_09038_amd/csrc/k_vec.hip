@@ -41,8 +41,7 @@ __global__ void k_mask_start(double *__restrict__ m, double *__restrict__ y, con
         y[i] = 0.0;
     }
 }
-template <class T>
-__global__ void k_set_list(T *y, T v, const int32_t *list, int n)
+__global__ void k_set_list(double *y, double v, const int32_t *list, int n)
 {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i < n) y[list[i]] = v;
@@ -458,13 +457,7 @@ hipError_t vec_mask_start(double *m, double *y, const double *x, const uint32_t 
 hipError_t vec_set_list(double *y, double v, const int32_t *list, int n, hipStream_t s)
 {
     if (n <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_set_list<double>, dim3(nblk(n)), dim3(256), 0, s, y, v, list, n);
-    return hipGetLastError();
-}
-hipError_t vec_set_list(float *y, float v, const int32_t *list, int n, hipStream_t s)
-{
-    if (n <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_set_list<float>, dim3(nblk(n)), dim3(256), 0, s, y, v, list, n);
+    hipLaunchKernelGGL(k_set_list, dim3(nblk(n)), dim3(256), 0, s, y, v, list, n);
     return hipGetLastError();
 }
 hipError_t vec_zero_list(double *y, const int32_t *list, int n, hipStream_t s) { return vec_set_list(y, 0.0, list, n, s); }

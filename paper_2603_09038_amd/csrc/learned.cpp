@@ -322,9 +322,9 @@ int ensure_coarse_graph(pa_lp *lp, hipStream_t s)
     return PA_OK;
 }
 
-// z (+)= P1 A1^{-1} P1^T r, then zero on the essential DOFs; with m, z = m * r + P1 A1^{-1} P1^T r
+// z = P1 A1^{-1} P1^T r, then zero on the essential DOFs; with m, z = m * r + P1 A1^{-1} P1^T r
 // and the essential DOFs are left to the caller, who calls ensure_coarse_graph when all is queued
-int coarse_part(pa_lp *lp, const double *r, double *z, bool add, hipStream_t s, const double *m = nullptr)
+int coarse_part(pa_lp *lp, const double *r, double *z, hipStream_t s, const double *m = nullptr)
 {
     HIP_OK(coarse_restrict(lp->box, lp->gll, r, lp->cr, lp->ct1, lp->ct2, s));
     if (lp->ncess) HIP_OK(vec_zero_list(lp->cr, lp->cess, lp->ncess, s));
@@ -333,7 +333,7 @@ int coarse_part(pa_lp *lp, const double *r, double *z, bool add, hipStream_t s, 
     if (rc) return rc;
     if (has_coarse_graph(lp) && !cap) HIP_OK(hipGraphLaunch(lp->cexec, s));
     else HIP_OK(coarse_solve(lp, s));
-    HIP_OK(coarse_prolong(lp->box, lp->gll, lp->cu, z, add, m, r, s));
+    HIP_OK(coarse_prolong(lp->box, lp->gll, lp->cu, z, m, r, s));
     if (!m && lp->op->ness) HIP_OK(vec_zero_list(z, lp->op->d_ess, lp->op->ness, s));
     return PA_OK;
 }
@@ -460,7 +460,7 @@ int hexpa::lp_precondition(pa_lp *lp, const double *r, double *z, hipStream_t s)
 {
     // Jacobi, plus the coarse correction (one pass over z), plus the network's learned one
     if (lp->o.use_coarse) {
-        int rc = coarse_part(lp, r, z, false, s, lp->dinv);
+        int rc = coarse_part(lp, r, z, s, lp->dinv);
         if (rc) return rc;
     } else {
         HIP_OK(vec_mul(z, lp->dinv, r, lp->ndof, s));
@@ -489,7 +489,7 @@ extern "C" int pa_lp_coarse(pa_lp *lp, const double *r, double *z, void *stream)
     PA_TRY
     if (!lp || !r || !z) return arg_error("pa_lp_coarse: NULL argument");
     if (lp->o.coarse_iters < 1) return arg_error("pa_lp_coarse: coarse_iters must be >= 1");
-    int rc = coarse_part(lp, r, z, false, as_stream(stream));
+    int rc = coarse_part(lp, r, z, as_stream(stream));
     return rc ? rc : ensure_coarse_graph(lp, as_stream(stream));
     PA_CATCH
 }
@@ -535,7 +535,7 @@ extern "C" int pa_lp_train_step(pa_lp *lp, const double *b, const double *xstar,
     HIP_OK(vec_mul(lp->v0, lp->dinv, rbuf, nd, s));
     HIP_OK(vec_sub(tbuf, tbuf, lp->v0, nd, s));
     if (lp->o.use_coarse) {
-        rc = coarse_part(lp, rbuf, lp->v0, false, s);
+        rc = coarse_part(lp, rbuf, lp->v0, s);
         if (rc) return rc;
         HIP_OK(vec_sub(tbuf, tbuf, lp->v0, nd, s));
     }
