@@ -280,7 +280,7 @@ typedef struct {
     int32_t loss;         /* PA_LP_LOSS_* */
     int32_t seed;         /* seed of the default (He-normal) parameter initialisation */
     int32_t infer_fp16;   /* 1: apply the network with FP16 MFMA (FP32 accumulation) in one
-                             fused kernel; 0: FP32 vector-ALU kernels (training always uses FP32) */
+                             fused kernel; 0: the FP32 MFMA kernels of training */
     double lr;            /* Adam step size (beta1 0.9, beta2 0.999, eps 1e-8) */
     double net_scale;     /* factor on the network's correction when the preconditioner is
                              applied (a damping, like omega of damped Jacobi); training
